@@ -111,6 +111,7 @@ int listed_grid(int beta, int shape) {
 }  // namespace
 
 const void* phg::multi_kernel_ptr(int beta, int shape, bool maps) {
+  if (is_deep(shape)) return multi_deep_ptr(beta);
   switch (beta) {
     case 1: return multi_beta<1>(shape, maps);
     case 2: return multi_beta<2>(shape, maps);

@@ -20,7 +20,10 @@ struct KernelShape {
   int track;   // one-pass shapes: 1 keeps change maps (rows that cannot
                // change are copied through untested); 2 also leaves tiles
                // and rows that cannot change untouched from the third pass
-               // on (the destination already holds them)
+               // on (the destination already holds them); 3: up to 16 / beta
+               // passes per launch that follow only what the pass before
+               // changed (deep_kernel.hpp), T of them where the caller
+               // chooses the passes of a launch
 };
 extern const KernelShape kShapes[];
 extern const int kNumShapes;

@@ -35,6 +35,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "phgrms_internal.hpp"
+
 namespace phg {
 
 constexpr int kRowBytes = 264;              // LDS row: pad 4 + 256 + pad 4
@@ -1071,7 +1073,7 @@ struct ImageDesc {
   int npasses;                   // passes for this image in this launch (0: idle)
   int prev_passes;               // passes of its previous launch (0: none)
   int tiles_x;
-  int pad;
+  int full_store;                // deep kernels: see DeepTile
   int* status;                   // or null: set to 1 if the image had converged before
                                  // this launch (its previous launch had a pass with no
                                  // change), else 0; written by the workgroup of tile 0
@@ -1082,6 +1084,11 @@ struct ImageDesc {
   uint8_t* map_out;
   int seq;
   int tile_base;                 // index of the image's tile 0 in the tile table
+  // deep kernels: maps of words (map_in, map_out) and of count bytes, and the
+  // tile geometry
+  const uint8_t* cnt_in;
+  uint8_t* cnt_out;
+  int depth, th;
 };
 
 // One tile of a multi-image launch: image index and tile index within it.
@@ -1094,6 +1101,7 @@ struct MultiArgs {
   const ImageDesc* images;
   const TileRef* tiles;
   int ntiles;
+  int check;                     // deep kernels: 1: a workgroup looks at several tiles at once
   int seq;                       // launch index (skipping kernels: the lists' rotation)
   uint32_t* list_state;          // skipping kernels: the group's TileLists (entries index
   int list_cap;                  // `tiles`), capacity ntiles; else null
@@ -1236,7 +1244,7 @@ struct FinishArgs {
                                      // before, same layout (one pass per launch), or null
   unsigned long long* changed;       // out: per-pass totals, k entries (may be null)
   int k;            // passes requested
-  int T;            // passes per launch
+  LaunchPlan plan;  // passes of each launch
   int launches;     // launches enqueued
   const uint8_t* buf_even_from_end;  // dst of launches j with (launches-1-j) even
   const uint8_t* buf_odd_from_end;   // dst of launches j with (launches-1-j) odd
@@ -1263,7 +1271,8 @@ struct FinishArgs {
   __syncthreads();
   const int z = s_first_zero;
   const int iters = (z < f.k) ? z + 1 : f.k;
-  int J = z / f.T + 1;  // launches that ran: launch j runs iff no zero before its first pass
+  // launches that ran: launch j runs iff no zero before its first pass
+  int J = f.plan.launch_of(z) + 1;
   if (J > f.launches) J = f.launches;
   if (f.k == 0) J = 0;
   if (blockIdx.x == 0 && threadIdx.x == 0 && f.iterations) *f.iterations = iters;

@@ -13,6 +13,7 @@
 #include "phgrms.h"
 #include "phgrms_internal.hpp"
 #include "pass_kernel.hpp"
+#include "deep_kernel.hpp"
 
 namespace phg {
 
@@ -39,8 +40,9 @@ int hip_fail(hipError_t e, const char* what) {
 const KernelShape kShapes[] = {
     {1, 8, 1, 0},  {1, 16, 1, 0}, {1, 8, 2, 0}, {1, 8, 4, 0}, {1, 16, 4, 0},
     {2, 16, 4, 0}, {4, 16, 4, 0}, {1, 8, 4, 1}, {1, 8, 2, 1}, {1, 4, 8, 0},
-    {1, 4, 4, 0},  {1, 8, 4, 2}, {1, 8, 2, 2},
+    {1, 4, 4, 0},  {1, 8, 4, 2}, {1, 8, 2, 2}, {4, 8, 8, 3},
 };
+static_assert(sizeof(kShapes) / sizeof(kShapes[0]) <= 16, "per-shape tables hold 16 entries");
 const int kNumShapes = int(sizeof(kShapes) / sizeof(kShapes[0]));
 
 namespace {
@@ -49,7 +51,7 @@ std::mutex g_tune_mu;
 // Shape index used by the fused path, per beta (1..PHGRMS_BETA_MAX) and
 // image size class (see size_class).
 int g_fused_shape[PHGRMS_BETA_MAX + 1][kSizeClasses] = {
-    {3, 3, 3}, {3, 3, 3}, {3, 3, 3}, {3, 3, 3}, {3, 3, 3}};
+    {13, 13, 13}, {13, 13, 13}, {13, 13, 13}, {13, 13, 13}, {13, 13, 13}};
 // Batch path: the skipping (1, 8, 2) at beta = 1 and 2 (the batch
 // autotuner's choice on a 512-image mixed batch, whole-batch Mpixel*iter/s
 // with one beta's shape varied: at beta = 2 1.30 M against 0.92 M with
@@ -85,6 +87,7 @@ const void* kernel_beta(int shape) {
 }
 
 const void* pass_kernel_ptr(int beta, int shape) {
+  if (is_deep(shape)) return deep_kernel_ptr(beta);
   switch (beta) {
     case 1: return kernel_beta<1>(shape);
     case 2: return kernel_beta<2>(shape);
@@ -176,22 +179,46 @@ hipError_t launch_pass(int beta, int shape, const PassArgs& a, hipStream_t s) {
   return hipLaunchKernel(k, dim3(grid), dim3(kShapes[shape].waves * 64), args, 0, s);
 }
 
+// A launch with a change map over more tiles than twice what fits on the
+// device at once: that many workgroups, each looking at several tiles (8192^2
+// at beta 2, nearly all of 8436 tiles idle: 23 us, 64 with one workgroup per
+// tile; 4 or 8 times what fits: 33 and 58).
+constexpr int kDeepOversubscription = 2;
+
+hipError_t launch_deep(int beta, int shape, DeepArgs a, hipStream_t s) {
+  const void* k = deep_kernel_ptr(beta);
+  int grid = pass_grid(beta, shape, a.ntiles);
+  const int full = pass_grid(beta, shape, 0, true) / kListedOversubscription * kDeepOversubscription;
+  if (k == nullptr || grid <= 0 || full <= 0) return hipErrorInvalidValue;
+  a.check = a.t.map_in != nullptr && grid > full ? 1 : 0;
+  if (a.check) grid = full;
+  void* args[] = {&a};
+  return hipLaunchKernel(k, dim3(grid), dim3(kDeepWaves * 64), args, 0, s);
+}
+
 }  // namespace
 
-int pass_grid(int beta, int shape, long long ntiles, bool persistent, bool cycle) {
+int device_cus() {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return -1;
-  int occ, cus;
+  std::lock_guard<std::mutex> lk(g_occ_mu);
+  if (g_cus[dev] == 0) {
+    int n = 0;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+      return -1;
+    g_cus[dev] = n;
+  }
+  return g_cus[dev];
+}
+
+int pass_grid(int beta, int shape, long long ntiles, bool persistent, bool cycle) {
+  const int cus = device_cus();
+  if (cus < 0) return -1;
+  int occ;
   {
     std::lock_guard<std::mutex> lk(g_occ_mu);
-    if (g_cus[dev] == 0) {
-      int n = 0;
-      if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        return -1;
-      g_cus[dev] = n;
-    }
     // the listed kernel's occupancy (its period-2 variant's apart)
-    const void* lkern = cycle ? cycle_kernel_ptr(beta, shape, 3) : skip_kernel_ptr(beta, shape, 3);
+    const void* lkern = is_deep(shape) ? pass_kernel_ptr(beta, shape) : cycle ? cycle_kernel_ptr(beta, shape, 3) : skip_kernel_ptr(beta, shape, 3);
     const int m = (persistent && lkern != nullptr) ? (cycle ? 2 : 1) : 0;
     if (g_occ[beta][shape][m] == 0) {
       int nb = 0;
@@ -202,7 +229,6 @@ int pass_grid(int beta, int shape, long long ntiles, bool persistent, bool cycle
       g_occ[beta][shape][m] = nb > 0 ? nb : 1;
     }
     occ = g_occ[beta][shape][m];
-    cus = g_cus[dev];
   }
   // Multiples of 8 so that every XCD gets the same number of workgroups.
   const long long need = (ntiles + 7) / 8 * 8;
@@ -229,9 +255,18 @@ int pass_grid(int beta, int shape, long long ntiles, bool persistent, bool cycle
   return int(g);
 }
 
-TileGeom tile_geom(const phgrms_params& p, int shape) {
+TileGeom tile_geom(const phgrms_params& p, int shape, int depth, bool alone) {
   const KernelShape& k = kShapes[shape];
   TileGeom g;
+  if (is_deep(shape)) {
+    g.T = depth > 0 ? depth : k.T;
+    g.TH = deep_rows(p.rows, p.cols, p.beta, g.T, alone ? device_cus() : 0);
+    g.TW = kDeepCols;
+    g.tiles_x = deep_tiles_x(p.cols);
+    g.tiles_y = int((static_cast<long long>(p.rows) + g.TH - 1) / g.TH);
+    g.ntiles = (long long)g.tiles_x * g.tiles_y;
+    return g;
+  }
   g.T = k.T;
   g.TH = k.waves * k.rows - 2 * (k.T - 1) * p.beta;
   g.TW = 256 - 2 * (k.T - 1) * p.beta;
@@ -295,8 +330,18 @@ void apply_tuning(const TuneTables& t) {
 // The plain path runs one pass per launch: the tuned shape if it is a
 // single-pass shape, else the default single-pass shape.
 int plain_shape(int beta, long long npx) {
-  const int s = fused_shape(beta, npx);
+  int s = fused_shape(beta, npx);
+  if (is_deep(s)) s = one_pass_shape(beta, npx, false);
   return (kShapes[s].T == 1 && !kShapes[s].track) ? s : kDefaultShape;
+}
+
+// (the autotuner's choices among the one-pass shapes: short waves below 2^20
+// pixels; with change tracking at beta 2 from there on, and skipping from 2^24)
+int one_pass_shape(int beta, long long npx, bool tracking) {
+  const int c = size_class(npx);
+  if (c == 0) return beta == 1 ? 10 : beta == 2 ? 9 : kDefaultShape;
+  if (!tracking || beta != 2) return kDefaultShape;
+  return c == 1 ? 7 : 12;
 }
 
 int validate_params(const phgrms_params& p) {
@@ -383,6 +428,7 @@ int enqueue_denoise(const uint8_t* d_in, uint8_t* d_out, const phgrms_params& p,
                     unsigned long long* diff2) {
   const long long n = (long long)p.rows * p.cols;
   hipError_t e;
+  if (is_deep(shape) && !deep_fits(p)) shape = kDefaultShape;
   if (diff2 != nullptr && cycle_kernel_ptr(p.beta, shape) == nullptr)
     return fail(PHGRMS_EINVAL, "no period-2 variant of kernel shape %d", shape);
   const bool lists = maps != nullptr && kShapes[shape].track == 2;
@@ -398,8 +444,10 @@ int enqueue_denoise(const uint8_t* d_in, uint8_t* d_out, const phgrms_params& p,
                        nl);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "init launch");
   }
+  const bool deep = is_deep(shape);
+  const LaunchPlan plan = deep ? deep_plan(p) : LaunchPlan{0, kShapes[shape].T, kShapes[shape].T};
+  const int L = p.k > 0 ? plan.launch_of(p.k - 1) + 1 : 0;
   const TileGeom g = tile_geom(p, shape);
-  const int L = (p.k + g.T - 1) / g.T;
   auto dst_of = [&](int j) -> uint8_t* { return ((L - 1 - j) % 2 == 0) ? d_out : ws_img; };
   const uint8_t* src = d_in;
   const uint8_t* src0 = d_in;    // source of launch 0 (after staging)
@@ -411,8 +459,36 @@ int enqueue_denoise(const uint8_t* d_in, uint8_t* d_out, const phgrms_params& p,
     src = ws_img;
     src0 = ws_img;
   }
+  // deep shapes: two change maps, one word and one count byte per row and tile column, in the
+  // space of the other shapes' maps and lists where they fit (without them
+  // every launch tests every pixel in its first pass)
+  const size_t deep_map = deep_map_words(p.rows, p.cols);
+  const bool deep_maps = deep && maps != nullptr &&
+                         2 * (sizeof(uint32_t) + 1) * deep_map <= change_map_bytes(p.rows, p.cols);
   if (n > 0) {
     for (int j = 0; j < L; ++j) {
+      if (deep && j >= plan.lead) {
+        const int start = plan.start(j);
+        const int depth = std::min(j == plan.lead ? plan.first : plan.rest, p.k - start);
+        const TileGeom gd = tile_geom(p, shape, depth, true);
+        uint32_t* words = reinterpret_cast<uint32_t*>(maps);
+        uint8_t* bytes = maps + 2 * sizeof(uint32_t) * deep_map;
+        const size_t in = size_t((j - 1) & 1) * deep_map, out = size_t(j & 1) * deep_map;
+        // (the dense lead launches write no map; the first two launches of a
+        // loop write buffers that hold nothing of it yet)
+        const bool has_map = deep_maps && j > plan.lead;
+        DeepArgs a;
+        a.t = DeepTile{src, dst_of(j), p.rows, p.cols, p.alpha, depth, depth, gd.TH, gd.tiles_x,
+                       has_map ? words + in : nullptr, deep_maps ? words + out : nullptr,
+                       has_map ? bytes + in : nullptr, deep_maps ? bytes + out : nullptr, j < 2 ? 1 : 0};
+        a.changed = counts;
+        a.pass0 = start;
+        a.ntiles = int(gd.ntiles);
+        a.check = 0;
+        if ((e = launch_deep(p.beta, shape, a, s)) != hipSuccess) return hip_fail(e, "pass launch");
+        src = a.t.dst;
+        continue;
+      }
       PassArgs a;
       a.src = src;
       a.dst = dst_of(j);
@@ -420,8 +496,8 @@ int enqueue_denoise(const uint8_t* d_in, uint8_t* d_out, const phgrms_params& p,
       a.rows = p.rows;
       a.cols = p.cols;
       a.alpha = p.alpha;
-      a.pass0 = j * g.T;
-      a.npasses = std::min(g.T, p.k - j * g.T);
+      a.pass0 = plan.start(j);
+      a.npasses = deep ? 1 : std::min(g.T, p.k - j * g.T);
       a.tiles_x = g.tiles_x;
       a.ntiles = int(g.ntiles);
       // one-pass launches keep change maps (alternating halves of `maps`).
@@ -431,8 +507,8 @@ int enqueue_denoise(const uint8_t* d_in, uint8_t* d_out, const phgrms_params& p,
       // kernel has none of the map bookkeeping.  They write no map, so the
       // launch after them tests every row as well.
       const size_t half = map_half_bytes(p.rows, p.cols);
-      const bool track = maps != nullptr && g.T == 1 && kShapes[shape].track;
-      const bool dense0 = track && j < kDenseFirstLaunches;
+      const bool track = maps != nullptr && !deep && g.T == 1 && kShapes[shape].track;
+      const bool dense0 = deep || (track && j < kDenseFirstLaunches);
       if (dense0) {
         const TileGeom gd = tile_geom(p, kDefaultShape);
         a.tiles_x = gd.tiles_x;
@@ -461,7 +537,7 @@ int enqueue_denoise(const uint8_t* d_in, uint8_t* d_out, const phgrms_params& p,
   f.diff2 = diff2;
   f.changed = changed;
   f.k = p.k;
-  f.T = g.T;
+  f.plan = plan;
   f.launches = L;
   f.buf_even_from_end = d_out;
   f.buf_odd_from_end = ws_img;
@@ -555,6 +631,7 @@ int phgrms_denoise_ex(const uint8_t* d_in, uint8_t* d_out, phgrms_params p, int3
     // the period-2 variants: the tuned skipping shape's own, else (1, 8, 4)
     // with change tracking if the tuned shape tracks changes, else without
     diff2 = reinterpret_cast<unsigned long long*>(ws + l.diff_off);
+    if (is_deep(shape)) shape = one_pass_shape(p.beta, (long long)p.rows * p.cols, true);
     if (kShapes[shape].track != 2) shape = kShapes[shape].track ? 7 : kDefaultShape;
   }
   return enqueue_denoise(d_in, d_out, p, shape, ws + l.img_off, counts, changed, iters,
@@ -657,7 +734,7 @@ int phgrms_denoise_plain(const uint8_t* d_in, uint8_t* d_out, phgrms_params p, v
   f.diff2 = nullptr;
   f.changed = changed;
   f.k = p.k;
-  f.T = 1;
+  f.plan = LaunchPlan{0, 1, 1};
   f.launches = L;
   f.buf_even_from_end = d_out;
   f.buf_odd_from_end = ws_img;
@@ -700,7 +777,7 @@ int phgrms_run_passes(const uint8_t* d_src, uint8_t* d_dst, phgrms_params p, int
   const uintptr_t a = reinterpret_cast<uintptr_t>(d_src), b = reinterpret_cast<uintptr_t>(d_dst);
   if (a < b + uintptr_t(n) && b < a + uintptr_t(n))
     return fail(PHGRMS_EINVAL, "source and destination overlap");
-  if (d_maps != nullptr && (!kShapes[shape].track || p.k != 1))
+  if (d_maps != nullptr && (!kShapes[shape].track || is_deep(shape) || p.k != 1))
     return fail(PHGRMS_EINVAL, "change maps need a change-tracking shape and k = 1");
   if (pass_index < 0) return fail(PHGRMS_EINVAL, "negative pass index");
   const size_t half = map_half_bytes(p.rows, p.cols);
@@ -709,7 +786,19 @@ int phgrms_run_passes(const uint8_t* d_src, uint8_t* d_dst, phgrms_params p, int
   if (d_maps != nullptr && ((m < a + uintptr_t(n) && a < m + mbytes) ||
                             (m < b + uintptr_t(n) && b < m + mbytes)))
     return fail(PHGRMS_EINVAL, "change maps overlap an image");
-  const TileGeom g = tile_geom(p, shape);
+  const TileGeom g = tile_geom(p, shape, p.k);
+  if (is_deep(shape)) {
+    if (!deep_fits(p)) return fail(PHGRMS_EUNSUPPORTED, "shape %d needs sides below 2^30", shape);
+    DeepArgs a;
+    a.t = DeepTile{d_src, d_dst, p.rows, p.cols, p.alpha, p.k, p.k, g.TH, g.tiles_x, nullptr,
+                   nullptr, nullptr, nullptr, 1};
+    a.changed = reinterpret_cast<unsigned long long*>(d_changed);
+    a.pass0 = 0;
+    a.ntiles = int(g.ntiles);
+    a.check = 0;
+    const hipError_t ed = launch_deep(p.beta, shape, a, static_cast<hipStream_t>(stream));
+    return ed == hipSuccess ? PHGRMS_OK : hip_fail(ed, "pass launch");
+  }
   PassArgs pa;
   pa.src = d_src;
   pa.dst = d_dst;
@@ -764,7 +853,7 @@ int phgrms_num_shapes(void) { return kNumShapes; }
 
 int phgrms_shape_tracks_changes(int32_t shape) {
   if (shape < 0 || shape >= kNumShapes) return fail(PHGRMS_EINVAL, "bad shape %d", shape);
-  return kShapes[shape].track != 0 ? 1 : 0;
+  return kShapes[shape].track != 0 && !is_deep(shape) ? 1 : 0;
 }
 
 int phgrms_shape_skips_unchanged(int32_t shape) {

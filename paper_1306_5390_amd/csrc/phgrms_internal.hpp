@@ -31,7 +31,22 @@ struct TileGeom {
   int tiles_x, tiles_y;
   long long ntiles;
 };
-TileGeom tile_geom(const phgrms_params& p, int shape);
+// For a deep shape: tiles laid out for `depth` passes (0: the shape's T), of
+// the rows that spread one image over the device (alone: the image has the
+// launch to itself) or of the most rows they can own.
+TileGeom tile_geom(const phgrms_params& p, int shape, int depth = 0, bool alone = false);
+
+// How a pass loop of k passes is cut into launches: `lead` launches of one
+// pass, one launch of `first`, then launches of `rest` each.
+struct LaunchPlan {
+  int lead, first, rest;
+  __host__ __device__ int start(int j) const {   // first pass of launch j
+    return j <= lead ? j : lead + first + (j - lead - 1) * rest;
+  }
+  __host__ __device__ int launch_of(int pass) const {
+    return pass < lead ? pass : pass < lead + first ? lead : lead + 1 + (pass - lead - first) / rest;
+  }
+};
 
 struct WsLayout {
   size_t state_off;    // int32 iteration count
@@ -72,6 +87,32 @@ void apply_tuning(const TuneTables& t);
 // multi_pass_kernel<beta, shape> (batch.hip).
 // maps: the kernel keeps change maps per image (tracking shapes only).
 const void* multi_kernel_ptr(int beta, int shape, bool maps = false);
+// Deep shapes (deep_kernel.hpp, deep.hip): kernels of one image and of many.
+inline bool is_deep(int shape) { return kShapes[shape].track == 3; }
+constexpr int kDeepWaves = 8;      // waves of a workgroup
+const void* deep_kernel_ptr(int beta);
+const void* multi_deep_ptr(int beta);
+// A tile's row and column arithmetic stays inside an int.
+bool deep_fits(const phgrms_params& p);
+// The launches of the pass loop.  `lead` dense launches of one pass come
+// first where every pixel has to be tested and the image is large: the dense
+// kernel tests it with no halo (2048^2, beta 2, k 32: 105 us with two,
+// 115 with none; 8192^2 433 and 463), while on smaller images the launches
+// cost more than the halo (1024^2: 80 and 73).  At beta 1 the dense pass is
+// cheaper, so that this pays from 2^25 pixels (8192^2: 1176 and 1234; 4099 x
+// 4001: 396 and 378).  The last launches have an even number of passes, so
+// that tiles that only alternate need not run.
+LaunchPlan deep_plan(const phgrms_params& p);
+// Owned rows of a tile of an image alone on the device: the fewest (but 4)
+// that give every CU at most one tile, else the most that a tile can own.
+// (997 x 1031, beta 3: 46 us with 250 tiles, 51 with 125 or with 315.)
+int deep_rows(int rows, int cols, int beta, int depth, int cus);
+// Words of a change map (a map has a word and a count byte per image row and
+// tile column).
+size_t deep_map_words(int rows, int cols);
+int device_cus();                  // of the current device, or -1
+// The one-pass shape that stands in for a deep one.
+int one_pass_shape(int beta, long long npx, bool tracking);
 // Grid size for a pass kernel shape over `ntiles` tiles: one workgroup per
 // tile, or at most the resident grid (CUs x resident workgroups) in grid
 // mode 1.  persistent (a launch over listed tiles): kListedOversubscription

@@ -124,7 +124,8 @@ size_t request_bytes(const phgrms_params& p) {
 // else the default shape with that many passes: (1, 8, 4) for one pass
 // (measured best for serving mixed sizes), the first such shape otherwise.
 int shape_for(int beta, long long npx, int passes) {
-  const int tuned = fused_shape(beta, npx);
+  int tuned = fused_shape(beta, npx);
+  if (passes == 1 && is_deep(tuned)) tuned = one_pass_shape(beta, npx, true);
   if (passes <= 0 || kShapes[tuned].T == passes) return tuned;
   if (passes == 1) return kDefaultShape;
   for (int s = 0; s < kNumShapes; ++s)
@@ -337,6 +338,9 @@ int run_step(phgrms_server* S, std::unique_lock<std::mutex>& lk) {
       x.npasses = std::min(r.T, r.p.k - j * r.T);
       x.prev_passes = j >= 1 ? std::min(r.T, r.p.k - (j - 1) * r.T) : 0;
       x.tiles_x = tg.tiles_x;
+      x.depth = tg.T;
+      x.th = tg.TH;
+      x.full_store = 1;
       x.status = dstat + ni;
       launched.push_back(id);
       himgs[ni++] = x;
@@ -420,6 +424,7 @@ int run_step(phgrms_server* S, std::unique_lock<std::mutex>& lk) {
     a.images = reinterpret_cast<const ImageDesc*>(d + o_imgs) + L.imgs_base;
     a.tiles = reinterpret_cast<const TileRef*>(d + o_tiles) + L.tiles_base;
     a.ntiles = int(L.ntiles);
+    a.check = 0;
     void* args[] = {&a};
     const long long grid = std::min<long long>((L.ntiles + 7) / 8 * 8,
                                                max_workgroups(kShapes[L.shape].waves * 64));
