@@ -4,9 +4,9 @@
 // alpha, beta and k.  Instead of one launch sequence per image, the images
 // are spread over three streams (balanced by work) and, per stream, launch j
 // of every image with the same beta and kernel shape goes into one
-// multi_pass_kernel launch over a static table of all their tiles.  The plan
-// precomputes, per group, the tile table and the image descriptors of every
-// launch index; a run uploads them once per set of pointers and replays the
+// multi_deep_kernel (or multi_pass_kernel) launch over a static table of all
+// their tiles.  The plan precomputes, per group, the tile tables and the
+// image descriptors of every launch index; a run uploads them once per set of pointers and replays the
 // whole sequence (forked to the streams and joined) as a HIP graph.
 #include <hip/hip_runtime.h>
 
@@ -108,6 +108,24 @@ int listed_grid(int beta, int shape) {
   return int(std::max<long long>(g, kListShards));
 }
 
+// Workgroups of a deep launch that looks at several tiles per workgroup
+// (kDeepOversubscription times as many as fit on the device at once), the
+// occupancy queried once per beta.
+int multi_deep_grid(int beta) {
+  static std::mutex mu;
+  static int occ[PHGRMS_BETA_MAX + 1] = {};
+  const int cus = device_cus();
+  if (cus < 0) return -1;
+  std::lock_guard<std::mutex> lk(mu);
+  if (occ[beta] == 0) {
+    int nb = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, multi_deep_ptr(beta), kDeepWaves * 64, 0) != hipSuccess)
+      return -1;
+    occ[beta] = nb > 0 ? nb : 1;
+  }
+  return std::max(8, occ[beta] * cus * kDeepOversubscription / 8 * 8);
+}
+
 }  // namespace
 
 const void* phg::multi_kernel_ptr(int beta, int shape, bool maps) {
@@ -131,19 +149,46 @@ size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 // with another's arithmetic.
 constexpr int kSideStreams = 3;
 
+// A static table of the tiles of a group's images, in one tile geometry.
+struct TileTable {
+  std::vector<TileRef> tiles;       // image = index into the group's images
+  size_t off = 0;                   // in the workspace
+};
+
 struct Group {
   int beta = 0;
   int shape = 0;
-  int T = 1;
+  LaunchPlan plan{0, 1, 1};         // passes of each launch, the same for all its images
   bool maps = false;                // change maps per image (tracking shapes)
   bool lists = false;               // tile lists (skipping shapes): lists_off, capacity tiles.size()
   size_t lists_off = 0;
-  int launches = 0;                 // max over its images of ceil(k/T)
+  int launches = 0;                 // max over its images
   std::vector<int> images;          // item indices
-  std::vector<TileRef> tiles;       // tile table (image = index into `images`)
-  size_t tiles_off = 0;             // workspace offsets
+  // tile tables: of the lead launches, of the next one, of those after it
+  // (a shape that is not deep has the first only)
+  TileTable tables[3];
   size_t descs_off = 0;             // launches x images.size() ImageDesc
+  bool deep() const { return is_deep(shape); }
+  int kind(int j) const { return !deep() || j < plan.lead ? 0 : j == plan.lead ? 1 : 2; }
+  const TileTable& table(int j) const { return tables[kind(j)]; }
+  int depth(int j) const { return j < plan.lead ? 1 : j == plan.lead ? plan.first : plan.rest; }
+  int kernel_shape(int j) const { return deep() && j < plan.lead ? kDefaultShape : shape; }
 };
+
+// How a group's loops are cut into launches.  Deep: in a large batch two
+// dense one-pass launches come first, since its images fill the device and
+// the halo of a deep tile is all cost while every pixel is tested, and at
+// beta 1 the later launches take 16 passes (150 images of 192 Mpixel, k 32:
+// 2.39 ms; without the dense launches 2.99, with 8 passes 2.48).  A small
+// batch is latency-bound, and takes fewer launches of smaller halo (12 images
+// of 1.5 Mpixel, k 16: 176 us against 204; 48 images of 20 Mpixel: 413
+// against 379).
+LaunchPlan group_plan(int beta, int shape, long long batch_px) {
+  if (!is_deep(shape)) return LaunchPlan{0, kShapes[shape].T, kShapes[shape].T};
+  if (beta >= 3) return LaunchPlan{0, 4, 4};
+  if (batch_px < (1ll << 24)) return LaunchPlan{0, 8, 8};
+  return LaunchPlan{2, 6, beta == 1 ? 16 : 8};
+}
 
 }  // namespace
 
@@ -155,8 +200,8 @@ struct phgrms_plan {
   std::vector<size_t> map_half;     // per item, bytes of one change map
   std::vector<int> tile_base;       // per item, index of its first tile in its group's table
   std::vector<int64_t> k_off;       // per item, offset in d_changed
-  std::vector<int> launches;        // per item, ceil(k/T)
-  std::vector<int> T;               // per item
+  std::vector<int> launches;        // per item
+  std::vector<char> staged;         // per item: staged for the uploaded pointers
   std::vector<Group> groups;
   size_t stage_off = 0;             // CopyDesc[n]
   size_t finish_off = 0;            // BatchFinishDesc[n]
@@ -200,24 +245,26 @@ int enqueue_run(phgrms_plan* pl, uint8_t* ws, hipStream_t s) {
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "batch zero launch");
     // and the counts and marks of the groups' tile lists
     for (auto& g : pl->groups) {
-      if (!g.lists || g.tiles.empty()) continue;
-      const long long nl = (long long)((size_t(TileLists::kHead) + g.tiles.size() + 1) / 2);
+      if (!g.lists || g.tables[0].tiles.empty()) continue;
+      const long long nl = (long long)((size_t(TileLists::kHead) + g.tables[0].tiles.size() + 1) / 2);
       hipLaunchKernelGGL(zero_u64_kernel, dim3(int(std::min<long long>((nl + 255) / 256, 1024))),
                          dim3(256), 0, s, reinterpret_cast<unsigned long long*>(ws + g.lists_off), nl);
       if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "batch list clear launch");
     }
   }
   // 2. stage in-place inputs whose first launch writes the output buffer
-  hipLaunchKernelGGL(multi_copy_kernel, dim3(32, std::min(n, 65535)), dim3(256), 0, s,
-                     reinterpret_cast<const CopyDesc*>(ws + pl->stage_off), n);
-  if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "batch stage launch");
+  if (std::find(pl->staged.begin(), pl->staged.end(), 1) != pl->staged.end()) {
+    hipLaunchKernelGGL(multi_copy_kernel, dim3(32, std::min(n, 65535)), dim3(256), 0, s,
+                       reinterpret_cast<const CopyDesc*>(ws + pl->stage_off), n);
+    if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "batch stage launch");
+  }
   // 3. launch j of every group; with several groups, each group on its side
   //    stream (forked from s after the staging, joined before the finish)
   int maxL = 0;
   unsigned used = 0;   // bit k: side stream k has a group with tiles
   for (auto& g : pl->groups) maxL = std::max(maxL, g.launches);
   for (size_t gi = 0; gi < pl->groups.size(); ++gi)
-    if (!pl->groups[gi].tiles.empty()) used |= 1u << pl->group_stream[gi];
+    if (!pl->groups[gi].table(0).tiles.empty()) used |= 1u << pl->group_stream[gi];
   const bool fork = (used & (used - 1)) != 0 && pl->fork != nullptr;
   if (fork) {
     if ((e = hipEventRecord(pl->fork, s)) != hipSuccess) return hip_fail(e, "batch fork");
@@ -228,24 +275,34 @@ int enqueue_run(phgrms_plan* pl, uint8_t* ws, hipStream_t s) {
   for (int j = 0; j < maxL; ++j) {
     for (size_t gi = 0; gi < pl->groups.size(); ++gi) {
       auto& g = pl->groups[gi];
-      if (j >= g.launches || g.tiles.empty()) continue;
+      const TileTable& tt = g.table(j);
+      if (j >= g.launches || tt.tiles.empty()) continue;
       const hipStream_t gs = fork ? pl->side[pl->group_stream[gi]] : s;
       MultiArgs a;
       a.images = reinterpret_cast<const ImageDesc*>(ws + g.descs_off) + size_t(j) * g.images.size();
-      a.tiles = reinterpret_cast<const TileRef*>(ws + g.tiles_off);
-      a.ntiles = int(g.tiles.size());
+      a.tiles = reinterpret_cast<const TileRef*>(ws + tt.off);
+      a.ntiles = int(tt.tiles.size());
+      a.check = 0;
       a.seq = j;
       a.list_state = g.lists ? reinterpret_cast<uint32_t*>(ws + g.lists_off) : nullptr;
       a.list_cap = a.ntiles;
+      const int shape = g.kernel_shape(j);
       int grid = int(std::min<long long>((a.ntiles + 7) / 8 * 8,
-                                         max_workgroups(kShapes[g.shape].waves * 64)));
+                                         max_workgroups(kShapes[shape].waves * 64)));
+      if (is_deep(shape) && j > g.plan.lead) {
+        // many tiles, most of them idle: a workgroup looks at several
+        const int full = multi_deep_grid(g.beta);
+        if (full <= 0) return fail(PHGRMS_EDEVICE, "occupancy query of the deep batch kernel failed");
+        a.check = grid > full ? 1 : 0;
+        if (a.check) grid = full;
+      }
       if (g.lists && j >= 3 && (grid = listed_grid(g.beta, g.shape)) <= 0)
         return fail(PHGRMS_EDEVICE, "occupancy query of the listed batch kernel failed");
       // (change-tracking groups: the dense kernel for the first launches)
       const void* k = g.lists ? multi_skip_ptr(g.beta, g.shape, j)
-                              : multi_kernel_ptr(g.beta, g.shape, g.maps && j >= kDenseFirstLaunches);
+                              : multi_kernel_ptr(g.beta, shape, g.maps && j >= kDenseFirstLaunches);
       void* args[] = {&a};
-      e = hipLaunchKernel(k, dim3(grid), dim3(kShapes[g.shape].waves * 64), args, 0, gs);
+      e = hipLaunchKernel(k, dim3(grid), dim3(kShapes[shape].waves * 64), args, 0, gs);
       if (e != hipSuccess) return hip_fail(e, "batch pass launch");
     }
   }
@@ -308,7 +365,10 @@ int phgrms_batch_plan(const phgrms_item* items, int32_t n, const char* tune_cach
     const int rc = read_tuning_file(tune_cache_path, tune);
     if (rc != PHGRMS_OK) return rc;
   }
-  auto batch_shape = [&](int beta, long long npx) { return tune.batch[beta][size_class(npx)]; };
+  auto batch_shape = [&](const phgrms_params& p) {
+    const int s = tune.batch[p.beta][size_class((long long)p.rows * p.cols)];
+    return is_deep(s) && !deep_fits(p) ? kDefaultShape : s;
+  };
   phgrms_plan* pl = new phgrms_plan();
   pl->items.assign(items, items + n);
   pl->counts_off.resize(n);
@@ -318,7 +378,7 @@ int phgrms_batch_plan(const phgrms_item* items, int32_t n, const char* tune_cach
   pl->tile_base.assign(n, 0);
   pl->k_off.resize(n);
   pl->launches.resize(n);
-  pl->T.resize(n);
+  pl->staged.assign(n, 0);
   // workspace: count slots of every item, then ping-pong images
   size_t off = 0;
   int64_t koff = 0;
@@ -337,14 +397,16 @@ int phgrms_batch_plan(const phgrms_item* items, int32_t n, const char* tune_cach
   // launches) first, each to the stream with the least work so far; a group
   // is the images of one stream that share (beta, kernel shape), one
   // multi-image launch per launch index.
+  long long batch_px = 0;
+  for (int i = 0; i < n; ++i) batch_px += (long long)items[i].p.rows * items[i].p.cols;
   std::vector<int> order(n), stream_of(n, 0);
   std::vector<double> work(n, 0.0), load(kSideStreams, 0.0);
   for (int i = 0; i < n; ++i) {
     order[i] = i;
-    const int shp = batch_shape(items[i].p.beta, (long long)items[i].p.rows * items[i].p.cols);
-    const int T = kShapes[shp].T;
-    if ((int64_t)items[i].p.rows * items[i].p.cols > 0)
-      work[i] = double(tile_geom(items[i].p, shp).ntiles) * double((items[i].p.k + T - 1) / T);
+    const int shp = batch_shape(items[i].p);
+    const LaunchPlan lp = group_plan(items[i].p.beta, shp, batch_px);
+    if ((int64_t)items[i].p.rows * items[i].p.cols > 0 && items[i].p.k > 0)
+      work[i] = double(tile_geom(items[i].p, shp, lp.rest).ntiles) * double(lp.launch_of(items[i].p.k - 1) + 1);
   }
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return work[a] > work[b]; });
   for (int i : order) {
@@ -355,52 +417,65 @@ int phgrms_batch_plan(const phgrms_item* items, int32_t n, const char* tune_cach
   std::map<std::tuple<int, int, int>, int> gidx;
   for (int i = 0; i < n; ++i) {
     const int b = items[i].p.beta;
-    const int shp = batch_shape(b, (long long)items[i].p.rows * items[i].p.cols);
+    const int shp = batch_shape(items[i].p);
     const auto key = std::make_tuple(stream_of[i], b, shp);
     if (!gidx.count(key)) {
       gidx[key] = int(pl->groups.size());
       Group g;
       g.beta = b;
       g.shape = shp;
-      g.T = kShapes[g.shape].T;
-      g.maps = kShapes[g.shape].track != 0 && g.T == 1;
-      g.lists = kShapes[g.shape].track == 2 && g.T == 1;
+      g.plan = group_plan(b, shp, batch_px);
+      g.maps = kShapes[g.shape].track != 0;
+      g.lists = kShapes[g.shape].track == 2;
       pl->groups.push_back(g);
       pl->group_stream.push_back(stream_of[i]);
     }
     Group& g = pl->groups[gidx[key]];
     const int local = int(g.images.size());
     g.images.push_back(i);
-    pl->T[i] = g.T;
-    pl->launches[i] = (items[i].p.k + g.T - 1) / g.T;
+    pl->launches[i] = items[i].p.k > 0 ? g.plan.launch_of(items[i].p.k - 1) + 1 : 0;
     g.launches = std::max(g.launches, pl->launches[i]);
-    const TileGeom tg = tile_geom(items[i].p, g.shape);
-    pl->tile_base[i] = int(g.tiles.size());
-    if ((int64_t)items[i].p.rows * items[i].p.cols > 0)
-      for (long long t = 0; t < tg.ntiles; ++t) g.tiles.push_back(TileRef{local, int(t)});
-    if (g.maps && (int64_t)items[i].p.rows * items[i].p.cols > 0) {
+    pl->tile_base[i] = int(g.tables[0].tiles.size());
+    if ((int64_t)items[i].p.rows * items[i].p.cols == 0) continue;
+    // a table for each kind of launch that some image of the group has
+    for (int kind = 0; kind < 3; ++kind) {
+      const int j = kind == 0 ? 0 : g.plan.lead + kind - 1;   // its first launch
+      if (g.kind(j) != kind || j >= pl->launches[i]) continue;
+      const TileGeom tg = tile_geom(items[i].p, g.kernel_shape(j), g.depth(j));
+      for (long long t = 0; t < tg.ntiles; ++t) g.tables[kind].tiles.push_back(TileRef{local, int(t)});
+    }
+    if (g.deep()) {
+      // two maps alternating by launch: a word and a byte per (row, tile column)
+      pl->map_half[i] = deep_map_words(items[i].p.rows, items[i].p.cols);
+      pl->map_off[i] = off;
+      off = up256(off + 2 * (sizeof(uint32_t) + 1) * pl->map_half[i]);
+    } else if (g.maps) {
       // one byte per (row, tile column), two maps alternating by launch
       // (never cleared: each byte carries its launch's stamp)
-      pl->map_half[i] = size_t(items[i].p.rows) * size_t(tg.tiles_x);
+      pl->map_half[i] = size_t(items[i].p.rows) * size_t(tile_geom(items[i].p, g.shape).tiles_x);
       pl->map_off[i] = off;
       off = up256(off + 2 * pl->map_half[i]);
     }
   }
   for (auto& g : pl->groups) {
-    if (g.tiles.size() > size_t(1) << 30) {
-      delete pl;
-      return fail(PHGRMS_EINVAL, "batch too large (%zu tiles)", g.tiles.size());
-    }
+    for (const TileTable& tt : g.tables)
+      if (tt.tiles.size() > size_t(1) << 30) {
+        const size_t ntiles = tt.tiles.size();
+        delete pl;
+        return fail(PHGRMS_EINVAL, "batch too large (%zu tiles)", ntiles);
+      }
     if (g.lists) {
       // tile lists over the group's tile table (cleared at every run)
       g.lists_off = off;
-      off = up256(off + 4 * TileLists::words(int(g.tiles.size())));
+      off = up256(off + 4 * TileLists::words(int(g.tables[0].tiles.size())));
     }
-    g.tiles_off = off;
-    off = up256(off + sizeof(TileRef) * g.tiles.size());
+    for (TileTable& tt : g.tables) {
+      tt.off = off;
+      off = up256(off + sizeof(TileRef) * tt.tiles.size());
+    }
     g.descs_off = off;
     off = up256(off + sizeof(ImageDesc) * size_t(std::max(g.launches, 1)) * g.images.size());
-    pl->total_launches += g.launches + ((g.lists && !g.tiles.empty()) ? 1 : 0);
+    pl->total_launches += g.launches + ((g.lists && !g.tables[0].tiles.empty()) ? 1 : 0);
   }
   pl->stage_off = off;
   off = up256(off + sizeof(CopyDesc) * size_t(n));
@@ -481,7 +556,7 @@ int phgrms_batch_run(phgrms_plan* pl, const uint8_t* d_in, size_t in_bytes, uint
     std::vector<CopyDesc> stage(n);
     std::vector<BatchFinishDesc> fin(n);
     for (auto& g : pl->groups) {
-      h.put(g.tiles_off, g.tiles.data(), g.tiles.size());
+      for (const TileTable& tt : g.tables) h.put(tt.off, tt.tiles.data(), tt.tiles.size());
       std::vector<ImageDesc> d(size_t(std::max(g.launches, 1)) * g.images.size());
       for (size_t li = 0; li < g.images.size(); ++li) {
         const int i = g.images[li];
@@ -495,11 +570,11 @@ int phgrms_batch_run(phgrms_plan* pl, const uint8_t* d_in, size_t in_bytes, uint
         const long long nb = (long long)p.rows * p.cols;
         const uint8_t* src0 = in;
         stage[i] = CopyDesc{in, wimg, 0};
-        if (nb > 0 && L > 0 && in == outp && dst_of(0) == outp) {
+        pl->staged[i] = nb > 0 && L > 0 && in == outp && dst_of(0) == outp;
+        if (pl->staged[i]) {
           stage[i].n = nb;
           src0 = wimg;
         }
-        const TileGeom tg = tile_geom(p, g.shape);
         for (int j = 0; j < g.launches; ++j) {
           ImageDesc x;
           std::memset(&x, 0, sizeof(x));
@@ -509,11 +584,31 @@ int phgrms_batch_run(phgrms_plan* pl, const uint8_t* d_in, size_t in_bytes, uint
           x.rows = p.rows;
           x.cols = p.cols;
           x.alpha = p.alpha;
-          x.pass0 = j * g.T;
-          x.npasses = (j < L) ? std::min(g.T, p.k - j * g.T) : 0;
-          x.prev_passes = (j >= 1 && j - 1 < L) ? std::min(g.T, p.k - (j - 1) * g.T) : 0;
+          auto passes = [&](int u) { return u < 0 || u >= L ? 0 : std::min(g.depth(u), p.k - g.plan.start(u)); };
+          x.pass0 = g.plan.start(j);
+          x.npasses = passes(j);
+          x.prev_passes = passes(j - 1);
+          const TileGeom tg = tile_geom(p, g.kernel_shape(j), g.depth(j));
           x.tiles_x = tg.tiles_x;
-          if (g.maps && pl->map_half[i] > 0) {
+          if (g.deep()) {
+            // (the lead launches write no map; the first two launches of a
+            // loop write buffers that hold nothing of it yet)
+            const size_t half = pl->map_half[i];
+            uint8_t* words = ws + pl->map_off[i];
+            uint8_t* bytes = words + 2 * sizeof(uint32_t) * half;
+            const size_t in = size_t((j - 1) & 1) * half, out = size_t(j & 1) * half;
+            if (j > g.plan.lead) {
+              x.map_in = words + sizeof(uint32_t) * in;
+              x.cnt_in = bytes + in;
+            }
+            if (j >= g.plan.lead) {
+              x.map_out = words + sizeof(uint32_t) * out;
+              x.cnt_out = bytes + out;
+            }
+            x.depth = tg.T;
+            x.th = tg.TH;
+            x.full_store = j < 2 ? 1 : 0;
+          } else if (g.maps && pl->map_half[i] > 0) {
             uint8_t* maps = ws + pl->map_off[i];
             // the first kDenseFirstLaunches launches run the dense kernel
             // and keep no maps
@@ -536,7 +631,7 @@ int phgrms_batch_run(phgrms_plan* pl, const uint8_t* d_in, size_t in_bytes, uint
         f.out = outp;
         f.n = nb;
         f.k = p.k;
-        f.T = g.T;
+        f.plan = g.plan;
         f.launches = L;
         fin[i] = f;
       }
@@ -545,8 +640,8 @@ int phgrms_batch_run(phgrms_plan* pl, const uint8_t* d_in, size_t in_bytes, uint
     h.put(pl->stage_off, stage.data(), stage.size());
     h.put(pl->finish_off, fin.data(), fin.size());
     // upload only the descriptor region (everything after the images)
-    size_t lo = pl->groups.empty() ? pl->stage_off : pl->groups.front().tiles_off;
-    for (auto& g : pl->groups) lo = std::min(lo, g.tiles_off);
+    size_t lo = pl->stage_off;
+    for (auto& g : pl->groups) lo = std::min(lo, g.tables[0].off);
     e = hipMemcpyAsync(ws + lo, h.bytes.data() + lo, pl->ws_bytes - lo, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return hip_fail(e, "batch descriptor upload");
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(e, "batch upload sync");

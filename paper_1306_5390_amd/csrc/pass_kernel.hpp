@@ -219,13 +219,6 @@ constexpr int kCountShards = 32;
 constexpr int kCountStride = 16;
 constexpr int kCountSlots = kCountShards * kCountStride;
 
-__device__ __forceinline__ unsigned long long pass_total(const unsigned long long* cnt, int t) {
-  unsigned long long s = 0;
-#pragma unroll
-  for (int k = 0; k < kCountShards; ++k) s += cnt[t * kCountSlots + k * kCountStride];
-  return s;
-}
-
 // 1 if pass t's count is zero, for a whole wave (every lane active): lane l <
 // kCountShards loads shard l, and the count is zero iff no shard is (they
 // are non-negative).  One load instruction and a ballot, in place of a
@@ -1254,19 +1247,33 @@ struct FinishArgs {
   int* iterations;  // may be null
 };
 
+// Sum of pass t's count shards over 8 neighbouring lanes (part: 0 .. 7), 4
+// shards each.
+__device__ __forceinline__ unsigned long long pass_total8(const unsigned long long* cnt, int t, int part) {
+  unsigned long long s = 0;
+#pragma unroll
+  for (int k = 0; k < kCountShards / 8; ++k) s += cnt[t * kCountSlots + (part + 8 * k) * kCountStride];
+#pragma unroll
+  for (int off = 1; off < 8; off <<= 1) s += __shfl_xor(s, off);
+  return s;
+}
+
 // Decide, from changed[], how many passes and launches ran, and move the
-// final image to `out` if it is elsewhere.
-[[maybe_unused]] static __global__ void finish_kernel(FinishArgs f) {
+// final image to `out` if it is elsewhere.  Every block derives the decision
+// itself, 8 threads per pass, so that a block waits for one round of loads
+// for up to 32 passes (a thread per pass, 32 loads each: 6 us at k 32, now 4).
+[[maybe_unused]] static __global__ __launch_bounds__(256) void finish_kernel(FinishArgs f) {
   __shared__ int s_first_zero;
   if (threadIdx.x == 0) s_first_zero = f.k;
   __syncthreads();
-  for (int t = threadIdx.x; t < f.k; t += blockDim.x) {
-    const unsigned long long tot = pass_total(f.counts, t);
-    if (blockIdx.x == 0 && f.changed) f.changed[t] = tot;
+  const int part = threadIdx.x & 7;
+  for (int t = threadIdx.x >> 3; t < f.k; t += 32) {
+    const unsigned long long tot = pass_total8(f.counts, t, part);
+    const bool same2 = f.diff2 != nullptr && t >= 1 && pass_total8(f.diff2, t, part) == 0ull;
+    if (part == 0 && blockIdx.x == 0 && f.changed) f.changed[t] = tot;
     // a pass that changed nothing, or (period-2 stop, t >= 1) whose image
     // equals the image two passes before, is the last one
-    if (tot == 0ull || (f.diff2 != nullptr && t >= 1 && pass_total(f.diff2, t) == 0ull))
-      atomicMin(&s_first_zero, t);
+    if (part == 0 && (tot == 0ull || same2)) atomicMin(&s_first_zero, t);
   }
   __syncthreads();
   const int z = s_first_zero;
@@ -1307,27 +1314,29 @@ struct BatchFinishDesc {
   const uint8_t* buf_odd_from_end;   // the other buffer
   uint8_t* out;
   long long n;
-  int k, T, launches, pad;
+  int k, launches;
+  LaunchPlan plan;
 };
 
 // grid (X, nimages): per image, the totals, the iteration count, and the
 // final image moved to `out` if it ended in the workspace.
-[[maybe_unused]] static __global__ void batch_finish_kernel(const BatchFinishDesc* descs, int nimages) {
+[[maybe_unused]] static __global__ __launch_bounds__(256) void batch_finish_kernel(const BatchFinishDesc* descs, int nimages) {
   __shared__ int s_first_zero;
   for (int y = blockIdx.y; y < nimages; y += gridDim.y) {
     const BatchFinishDesc f = descs[y];
     __syncthreads();
     if (threadIdx.x == 0) s_first_zero = f.k;
     __syncthreads();
-    for (int t = threadIdx.x; t < f.k; t += blockDim.x) {
-      const unsigned long long tot = pass_total(f.counts, t);
-      if (blockIdx.x == 0 && f.changed) f.changed[t] = tot;
-      if (tot == 0ull) atomicMin(&s_first_zero, t);
+    const int part = threadIdx.x & 7;
+    for (int t = threadIdx.x >> 3; t < f.k; t += 32) {
+      const unsigned long long tot = pass_total8(f.counts, t, part);
+      if (part == 0 && blockIdx.x == 0 && f.changed) f.changed[t] = tot;
+      if (part == 0 && tot == 0ull) atomicMin(&s_first_zero, t);
     }
     __syncthreads();
     const int z = s_first_zero;
     const int iters = (z < f.k) ? z + 1 : f.k;
-    int J = z / f.T + 1;
+    int J = f.plan.launch_of(z) + 1;
     if (J > f.launches) J = f.launches;
     if (f.k == 0) J = 0;
     if (blockIdx.x == 0 && threadIdx.x == 0 && f.iterations) *f.iterations = iters;

@@ -52,14 +52,11 @@ std::mutex g_tune_mu;
 // image size class (see size_class).
 int g_fused_shape[PHGRMS_BETA_MAX + 1][kSizeClasses] = {
     {13, 13, 13}, {13, 13, 13}, {13, 13, 13}, {13, 13, 13}, {13, 13, 13}};
-// Batch path: the skipping (1, 8, 2) at beta = 1 and 2 (the batch
-// autotuner's choice on a 512-image mixed batch, whole-batch Mpixel*iter/s
-// with one beta's shape varied: at beta = 2 1.30 M against 0.92 M with
-// change maps only and 0.82 M dense; at beta = 1 1.30 M against 1.24 M
-// for the skipping (1, 8, 4) and 1.23 M for four dense passes per
-// launch); (1, 8, 4) for larger beta.
+// Batch path: the deep shape too (48 images of 20 Mpixel, k 32: 0.38 ms
+// against 1.16 with the skipping (1, 8, 2); 150 images of 192 Mpixel: 2.4
+// against 5.1).
 int g_batch_shape[PHGRMS_BETA_MAX + 1][kSizeClasses] = {
-    {3, 3, 3}, {12, 12, 12}, {12, 12, 12}, {3, 3, 3}, {3, 3, 3}};
+    {13, 13, 13}, {13, 13, 13}, {13, 13, 13}, {13, 13, 13}, {13, 13, 13}};
 
 template <int B, int T, int R, int W, int TRACK = 0, bool CYC = false>
 const void* kernel_ptr() {
@@ -178,12 +175,6 @@ hipError_t launch_pass(int beta, int shape, const PassArgs& a, hipStream_t s) {
   void* args[] = {const_cast<PassArgs*>(&a)};
   return hipLaunchKernel(k, dim3(grid), dim3(kShapes[shape].waves * 64), args, 0, s);
 }
-
-// A launch with a change map over more tiles than twice what fits on the
-// device at once: that many workgroups, each looking at several tiles (8192^2
-// at beta 2, nearly all of 8436 tiles idle: 23 us, 64 with one workgroup per
-// tile; 4 or 8 times what fits: 33 and 58).
-constexpr int kDeepOversubscription = 2;
 
 hipError_t launch_deep(int beta, int shape, DeepArgs a, hipStream_t s) {
   const void* k = deep_kernel_ptr(beta);

@@ -19,6 +19,11 @@ constexpr int kDenseFirstLaunches = 2;
 // Workgroups of a launch over listed tiles, in multiples of the grid that
 // fits on the device at once.
 constexpr int kListedOversubscription = 4;
+// A launch with a change map over more tiles than twice what fits on the
+// device at once: that many workgroups, each looking at several tiles (8192^2
+// at beta 2, nearly all of 8436 tiles idle: 23 us, 64 with one workgroup per
+// tile; 4 or 8 times what fits: 33 and 58).
+constexpr int kDeepOversubscription = 2;
 // Largest grid (in workgroups of `threads` lanes) of a launch: fewer than
 // 2^31 work-items per dispatch (the dispatch size stays a positive 32-bit
 // count), a multiple of 16.  Only images near 2^31 pixels reach it; the

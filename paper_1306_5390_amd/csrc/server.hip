@@ -367,7 +367,7 @@ int run_step(phgrms_server* S, std::unique_lock<std::mutex>& lk) {
     f.out = r.out;
     f.n = (long long)r.p.rows * r.p.cols;
     f.k = r.p.k;
-    f.T = r.T;
+    f.plan = LaunchPlan{0, r.T, r.T};
     f.launches = r.L;
     hfin[nf++] = f;
     finishing.push_back(id);

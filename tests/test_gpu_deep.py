@@ -97,3 +97,64 @@ def test_many_tiles_per_workgroup(beta, k):
     ref = _run(img, 20, beta, k, shape=DENSE)
     got = _run(img, 20, beta, k)
     assert np.array_equal(got[0], ref[0]) and got[1:] == ref[1:]
+
+
+@pytest.mark.parametrize("big", [False, True])
+@pytest.mark.parametrize("in_place", [False, True])
+def test_batch_of_mixed_images(big, in_place):
+    """Every beta in one batch, with empty images, k 0 and k across launches;
+    `big` adds images that make the batch one with dense lead launches.  Two
+    runs (the second replays the captured graph)."""
+    torch, m = _modules()
+    specs, imgs = [], []
+    for i, (r, c, k) in enumerate([(70, 300, 5), (33, 225, 0), (0, 40, 7), (129, 448, 33), (5, 700, 9), (200, 223, 17),
+                                   (64, 64, 1), (150, 500, 40)]):
+        for beta in (1, 2, 3, 4):
+            specs.append((r, c, 12 + i, beta, k))
+            imgs.append(_oscillating(r, c, i) if i % 2 else synth.noisy_image(r, c, 0.3, 60 + i))
+    want = [oracle.denoise(im, s[2], s[3], s[4]) for s, im in zip(specs, imgs)]
+    if big:
+        im = np.tile(synth.noisy_image(512, 600, 0.3, 5), (6, 6))
+        for beta in (1, 2):
+            specs.append(im.shape + (20, beta, 21))
+            imgs.append(im)
+            want.append(_run(im, 20, beta, 21, shape=DENSE))
+    for b in (1, 2, 3, 4):
+        assert m.get_batch_tuning_class(b, 0) == DEEP
+    plan = m.Batch(specs)
+    src = plan.new_arena()
+    dst = src if in_place else plan.new_arena()
+    stream = torch.cuda.Stream()
+    for _ in range(2):
+        for i, im in enumerate(imgs):
+            plan.view(src, i).copy_(torch.from_numpy(im))
+        stream.wait_stream(torch.cuda.current_stream())
+        plan.run(src, dst, stream=stream)
+        torch.cuda.synchronize()
+        for i, ((it, ch), w) in enumerate(zip(plan.results(), want)):
+            assert np.array_equal(plan.view(dst, i, out=True).cpu().numpy(), w[0]), specs[i]
+            assert it == w[1] and list(ch) == list(w[2])[:it], specs[i]
+    plan.close()
+
+
+@pytest.mark.parametrize("passes", [0, 1, 4, -1])
+def test_served_requests(passes):
+    """Requests at different launches share a step's deep launch."""
+    _, m = _modules()
+    import time
+    import torch
+    srv = m.Server(96 << 20, passes_per_step=passes)
+    todo = {}
+    for i in range(24):
+        im = synth.noisy_image(40 + 17 * i, 230 + 29 * i, 0.25, i) if i % 3 else _oscillating(90, 300 + i, i)
+        p = (20, 1 + i % 4, 1 + 3 * (i % 7))
+        todo[srv.submit(torch.from_numpy(im).cuda(), *p)] = oracle.denoise(im, *p)
+    end = time.time() + 60
+    while todo and time.time() < end:
+        for rid in srv.next_done():
+            out, it, ch, _ = srv.poll(rid)
+            ref, rit, rch = todo.pop(rid)
+            assert np.array_equal(out.cpu().numpy(), ref) and it == rit and list(ch) == list(rch)[:it]
+            srv.release(rid)
+    assert not todo
+    srv.close()
