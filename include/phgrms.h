@@ -250,6 +250,10 @@ int phgrms_selftest(int64_t* d_failures, void* stream);
 int phgrms_cardinality(const uint8_t* d_img, int32_t rows, int32_t cols,
                        int32_t alpha, int32_t beta, uint16_t* d_card,
                        void* stream);
+/* The same into a device uint32 array. */
+int phgrms_cardinality_u32(const uint8_t* d_img, int32_t rows, int32_t cols,
+                           int32_t alpha, int32_t beta, uint32_t* d_card,
+                           void* stream);
 
 /* Algorithm 1 as printed (Section 2): every pixel p adds one to the
  * cardinality of each in-image pixel q of its (2*beta+1)^2 window whose grey

@@ -78,6 +78,8 @@ def load_library(path: str = LIB_PATH):
         lib.phgrms_denoise_async.restype = ctypes.c_int
         lib.phgrms_cardinality.argtypes = [vp, i32, i32, i32, i32, vp, vp]
         lib.phgrms_cardinality.restype = ctypes.c_int
+        lib.phgrms_cardinality_u32.argtypes = [vp, i32, i32, i32, i32, vp, vp]
+        lib.phgrms_cardinality_u32.restype = ctypes.c_int
         lib.phgrms_run_passes.argtypes = [vp, vp, Params, i32, i32, vp, vp, vp]
         lib.phgrms_run_passes.restype = ctypes.c_int
         lib.phgrms_change_map_bytes.argtypes = [Params]
@@ -273,12 +275,12 @@ def cardinality(img: torch.Tensor, alpha: int, beta: int, stream=None) -> torch.
     _check_image(img)
     lib = load_library()
     rows, cols = img.shape
-    card = torch.empty((rows, cols), dtype=torch.int16, device=img.device)
+    card = torch.empty((rows, cols), dtype=torch.int32, device=img.device)
     with torch.cuda.device(img.device):
-        rc = lib.phgrms_cardinality(img.data_ptr(), rows, cols, alpha, beta,
-                                    card.data_ptr(), _stream_handle(stream))
+        rc = lib.phgrms_cardinality_u32(img.data_ptr(), rows, cols, alpha, beta,
+                                        card.data_ptr(), _stream_handle(stream))
     check(rc)
-    return card.to(torch.int32) & 0xFFFF
+    return card
 
 
 def cardinality_scatter(img: torch.Tensor, alpha: int, beta: int, stream=None) -> torch.Tensor:

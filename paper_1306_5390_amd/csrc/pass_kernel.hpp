@@ -1369,30 +1369,4 @@ struct BatchFinishDesc {
   if (bad_sqrt) atomicAdd(fails + 1, (unsigned long long)bad_sqrt);
 }
 
-// Algorithm 1 by gathering: card[p] = #{q in window(p), q in image,
-// |I(q) - I(p)| < alpha}.  One thread per pixel, bytes read from HBM.
-[[maybe_unused]] static __global__ void cardinality_kernel(const uint8_t* __restrict__ img, int rows, int cols,
-                                   int alpha, int beta, uint16_t* __restrict__ card) {
-  const long long n = (long long)rows * cols;
-  for (long long p = blockIdx.x * (long long)blockDim.x + threadIdx.x; p < n;
-       p += (long long)gridDim.x * blockDim.x) {
-    const int r = int(p / cols);
-    const int c = int(p - (long long)r * cols);
-    const int x = img[p];
-    int cnt = 0;
-    // the window clipped to the image (in 64 bits: r + beta may pass INT_MAX)
-    const int i0 = r - beta < 0 ? 0 : r - beta;
-    const int i1 = int((long long)r + beta < rows ? (long long)r + beta : rows - 1);
-    const int j0 = c - beta < 0 ? 0 : c - beta;
-    const int j1 = int((long long)c + beta < cols ? (long long)c + beta : cols - 1);
-    for (int i = i0; i <= i1; ++i) {
-      for (int j = j0; j <= j1; ++j) {
-        const int y = img[(long long)i * cols + j];
-        cnt += (y < x + alpha && y > x - alpha) ? 1 : 0;
-      }
-    }
-    card[p] = uint16_t(cnt);
-  }
-}
-
 }  // namespace phg

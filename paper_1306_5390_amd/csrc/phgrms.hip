@@ -971,20 +971,4 @@ int phgrms_get_tuning(int32_t beta) {
   return fused_shape(beta, 1ll << 22);
 }
 
-int phgrms_cardinality(const uint8_t* d_img, int32_t rows, int32_t cols, int32_t alpha,
-                       int32_t beta, uint16_t* d_card, void* stream) {
-  phgrms_params p{rows, cols, alpha, beta, 0};
-  int rc = validate_params(p);
-  if (rc != PHGRMS_OK) return rc;
-  const long long n = (long long)rows * cols;
-  if (n == 0) return PHGRMS_OK;
-  if (d_img == nullptr || d_card == nullptr) return fail(PHGRMS_EINVAL, "null pointer");
-  const int blocks = int(std::min<long long>((n + 255) / 256, 65536));
-  hipLaunchKernelGGL(cardinality_kernel, dim3(blocks), dim3(256), 0,
-                     static_cast<hipStream_t>(stream), d_img, rows, cols, alpha, beta, d_card);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return hip_fail(e, "cardinality launch");
-  return PHGRMS_OK;
-}
-
 }  // extern "C"
