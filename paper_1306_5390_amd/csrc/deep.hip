@@ -9,14 +9,19 @@
 
 namespace phg {
 
-const void* deep_kernel_ptr(int beta) {
+template <int WAVES>
+static const void* deep_ptr(int beta) {
   switch (beta) {
-    case 1: return reinterpret_cast<const void*>(&deep_kernel<1, kDeepWaves>);
-    case 2: return reinterpret_cast<const void*>(&deep_kernel<2, kDeepWaves>);
-    case 3: return reinterpret_cast<const void*>(&deep_kernel<3, kDeepWaves>);
+    case 1: return reinterpret_cast<const void*>(&deep_kernel<1, WAVES>);
+    case 2: return reinterpret_cast<const void*>(&deep_kernel<2, WAVES>);
+    case 3: return reinterpret_cast<const void*>(&deep_kernel<3, WAVES>);
     case 4: return reinterpret_cast<const void*>(&deep_kernel<4, kDeepWaves>);
     default: return nullptr;
   }
+}
+
+const void* deep_kernel_ptr(int beta, bool wide) {
+  return wide ? deep_ptr<kDeepWideWaves>(beta) : deep_ptr<kDeepWaves>(beta);
 }
 
 const void* multi_deep_ptr(int beta) {
@@ -47,7 +52,7 @@ LaunchPlan deep_plan(const phgrms_params& p) {
 }
 
 int deep_rows(int rows, int cols, int beta, int depth, int cus) {
-  const int most = kDeepWaves * kDeepRows - 2 * (depth - 1) * beta;
+  const int most = kDeepH - 2 * (depth - 1) * beta;
   const int tiles_x = deep_tiles_x(cols);
   const int tiles_y = cus / std::max(tiles_x, 1);
   if (tiles_y < 1 || rows / tiles_y >= most) return most;

@@ -13,7 +13,7 @@
 //   * by list, where at most kDeepListMost pixels of the tile changed: every
 //     pixel of their windows is evaluated exactly, one lane each, the items
 //     shared by all waves;
-//   * by strips of 8 rows, one per wave: a strip without an active pixel
+//   * by strips of 8 rows (4 with 16 waves), one per wave: a strip without an active pixel
 //     (within BETA of a change) does nothing; one with at most kDeepWords
 //     active words (4 pixels) takes the band test on those words alone, one
 //     lane each, and evaluates the candidates; any other one takes the band
@@ -47,7 +47,8 @@
 
 namespace phg {
 
-constexpr int kDeepRows = 8;                       // rows per wave: 8 rows x 8 words of bits = 64 lanes
+constexpr int kDeepH = 64;                         // rows computed: WAVES strips of R rows, R <= 8 (R rows x
+                                                   // 8 words of bits, one lane each)
 constexpr int kDeepHalo = 16;                      // halo columns on each side: passes * BETA fit in it
 constexpr int kDeepCols = 256 - 2 * kDeepHalo;     // owned columns of a tile
 constexpr int kDeepMaxPasses = 16;
@@ -365,8 +366,8 @@ __device__ __forceinline__ uint32_t pass_value(const uint32_t* src, int bc, int 
   return v;
 }
 
-// The active pixels of 8 computed rows from `strip` on, as bits: lane 8 ri +
-// wd has word wd of row strip + ri.  cur: the last pass's change bits.
+// The active pixels of up to 8 computed rows from `strip` on, as bits: lane 8
+// ri + wd has word wd of row strip + ri.  cur: the last pass's change bits.
 template <int BETA>
 __device__ __forceinline__ uint32_t active_word(const uint32_t* cur, int strip, int ri, int wd,
                                                 const DeepBounds& b) {
@@ -374,7 +375,6 @@ __device__ __forceinline__ uint32_t active_word(const uint32_t* cur, int strip, 
   uint32_t v = 0u;
 #pragma unroll
   for (int dr = -BETA; dr <= BETA; ++dr) v |= c[8 * dr];
-  if (__builtin_amdgcn_ballot_w64(v != 0u) == 0ull) return 0u;
   // the neighbouring words of the row (at a row's ends the lane next door has
   // another row's: such columns are outside what a pass must get right)
   const uint32_t vl = uint32_t(__builtin_amdgcn_update_dpp(0, int(v), 0x111, 0xF, 0xF, true));  // row_shr:1
@@ -472,11 +472,11 @@ __device__ __forceinline__ void push_candidates(uint32_t cand, uint32_t ent, uin
   sync_wave();
 }
 
-// The band test on every pixel of 8 computed rows from `strip` on, as in
+// The band test on every pixel of R computed rows from `strip` on, as in
 // pass_kernel.hpp.  Candidates go to the ring q (through dq) and to
 // evaluate(valid, LDS row << 8 | column) in rounds of 64; those left over are
 // entries [qhead, qtail) of q.  row(LDS row, lane's dword) takes every row.
-template <int BETA, class Eval, class Row>
+template <int BETA, int R, class Eval, class Row>
 __device__ __forceinline__ void dense_rows(const uint32_t* src, int strip, int lane, const DeepBounds& b,
                                            const Band& band, uint16_t* q, uint32_t* dq, int& qhead,
                                            int& qtail, Eval evaluate, Row row) {
@@ -510,11 +510,11 @@ __device__ __forceinline__ void dense_rows(const uint32_t* src, int strip, int l
 #pragma unroll
   for (int i = 0; i < 2 * BETA; ++i) load_row(i, win[i]);
 #pragma unroll 1
-  for (int j0 = 0; j0 < kDeepRows; j0 += NW) {
+  for (int j0 = 0; j0 < R; j0 += NW) {
 #pragma unroll
     for (int jj = 0; jj < NW; ++jj) {
       const int jc = j0 + jj;
-      if (jc < kDeepRows) {
+      if (jc < R) {
         load_row(jc + 2 * BETA, win[(jj + 2 * BETA) % NW]);
         const int i = strip + jc;
         const uint32_t X = win[(jj + BETA) % NW][BETA];
@@ -591,17 +591,18 @@ __device__ __forceinline__ uint32_t groups4(uint32_t x) {
   return ((x & 0x01010101u) * 0x10204080u) >> 28;
 }
 
-// ---- many waves per tile -------------------------------------------------------------
+// ---- a tile ---------------------------------------------------------------------------
 //
-// For a loop's first launch and for small images: every strip of 8 rows has
-// a wave of its own, and the tile two buffers.  A sparse strip needs no
-// copy-through: the destination buffer holds the image two passes back,
-// which differs from the source only where the last pass changed a pixel,
-// and every such pixel is active and is written.
+// 8 waves of 8 rows; or 16 waves of 4 rows, where a launch leaves every CU at
+// most one tile and a pass takes as long as a strip (1024^2, beta 2, k 32: 64
+// us against 72; 128^2, k 5: 19 against 22; at beta 4 the window's registers
+// spill, and 8 waves are faster, 31 us against 33 at 500 x 700, k 12).
 
 template <int BETA, int WAVES>
 struct DeepSmem {
-  static constexpr int BROWS = WAVES * kDeepRows + 2 * BETA;   // rows per LDS buffer
+  static constexpr int R = kDeepH / WAVES;                 // rows of a strip
+  static constexpr int BROWS = kDeepH + 2 * BETA;          // rows per LDS buffer
+  static_assert(R <= 8 && R * WAVES == kDeepH, "a lane has one word of bits");
   uint32_t buf0[BROWS * kRowWords + 1];
   uint32_t buf1[BROWS * kRowWords + 1];
   uint32_t chg[2][BROWS * 8];       // change bits: word d of a row, bit i: computed column 32d + i
@@ -651,9 +652,8 @@ template <int BETA, int WAVES>
 __device__ __forceinline__ void run_deep_tile(DeepSmem<BETA, WAVES>& sm, const DeepTile& a, int tile) {
   constexpr int NW = 2 * BETA + 1;
   constexpr int N = NW * NW;
-  constexpr int R = kDeepRows;
-  constexpr int H = WAVES * R;                 // rows computed
-  constexpr int BROWS = H + 2 * BETA;
+  constexpr int R = kDeepH / WAVES;
+  constexpr int BROWS = kDeepH + 2 * BETA;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -697,6 +697,7 @@ __device__ __forceinline__ void run_deep_tile(DeepSmem<BETA, WAVES>& sm, const D
   __syncthreads();
 
   const int ri = lane >> 3, wd = lane & 7;         // this lane's row of the strip and word of bits
+  const bool has_word = R == 8 || ri < R;
   const int strip = w * R;                         // this wave's first computed row
   const int mine = (strip + ri + BETA) * 8 + wd;
   uint32_t any_bits = 0u;                          // changes of the strip's passes (not of list passes)
@@ -748,8 +749,8 @@ __device__ __forceinline__ void run_deep_tile(DeepSmem<BETA, WAVES>& sm, const D
       // bit tells which came first.
       if (!listed) {
         // the list, from the change bits; and the bits of two passes back go
-        uint32_t m = cur[mine];
-        nxt[mine] = 0u;
+        uint32_t m = has_word ? cur[mine] : 0u;
+        if (has_word) nxt[mine] = 0u;
         any_bits |= m;
         if (m != 0u) {
           unsigned at = atomicAdd(&sm.fill, unsigned(__builtin_popcount(m)));
@@ -796,8 +797,8 @@ __device__ __forceinline__ void run_deep_tile(DeepSmem<BETA, WAVES>& sm, const D
       // ---- by strips -------------------------------------------------------------
       const bool live = strip < b.row_hi && strip + R > b.row_lo;   // some row counts in this pass
       const bool all = t == 0 && !has_map;           // no change bits yet: every pixel is active
-      if (!all) any_bits |= t > 0 ? cur[mine] : 0u;
-      nxt[mine] = 0u;
+      if (!all && has_word) any_bits |= t > 0 ? cur[mine] : 0u;
+      if (has_word) nxt[mine] = 0u;
       sync_wave();                                 // cleared before this wave sets bits
       if (live) {
         int qhead = 0, qtail = 0;
@@ -810,9 +811,9 @@ __device__ __forceinline__ void run_deep_tile(DeepSmem<BETA, WAVES>& sm, const D
           wave_changed += __builtin_popcountll(__builtin_amdgcn_ballot_w64(ch && owned(e)));
         };
         uint16_t* wq = reinterpret_cast<uint16_t*>(sm.lanes[w]);
-        const int words = all ? kDeepWords + 1 : queue_words(active_word<BETA>(cur, strip, ri, wd, b), wq, ri, wd);
+        const int words = all ? kDeepWords + 1 : queue_words(has_word ? active_word<BETA>(cur, strip, ri, wd, b) : 0u, wq, ri, wd);
         if (words > kDeepWords) {
-          dense_rows<BETA>(src, strip, lane, b, band, q, sm.lanes[w], qhead, qtail, evaluate,
+          dense_rows<BETA, R>(src, strip, lane, b, band, q, sm.lanes[w], qhead, qtail, evaluate,
                            [&](int lr, uint32_t X) { dst[lr * kRowWords + 1 + lane] = X; });
           moved = true;                            // (not looked at)
         } else {
@@ -864,17 +865,18 @@ __device__ __forceinline__ void run_deep_tile(DeepSmem<BETA, WAVES>& sm, const D
 
   // The strip's map words and owned rows.
   {
-    const uint32_t last = sm.chg[cb][mine];
+    const uint32_t last = has_word ? sm.chg[cb][mine] : 0u;
     // owned columns only: half of the first and of the last word
     const uint32_t ownm = wd == 0 ? 0xFFFF0000u : (wd == 7 ? 0x0000FFFFu : ~0u);
     const int i = strip + ri;
-    const uint32_t any = or8((any_bits | last) & ownm) | ((sm.row_any[(i + BETA) >> 5] >> ((i + BETA) & 31)) & 1u);
+    const uint32_t any = or8((any_bits | last) & ownm) |
+                         (has_word ? (sm.row_any[(i + BETA) >> 5] >> ((i + BETA) & 31)) & 1u : 0u);
     if (a.map_out != nullptr) {
       const uint32_t nib = groups4(last & ownm);
       const uint32_t word = or8(wd == 0 ? nib >> 2 : nib << (4 * wd - 2));
       const uint32_t c = add8(uint32_t(__builtin_popcount(last & ownm)));
       const int r = g.row_first + BETA + i;
-      if (wd == 0 && i >= g.own && i < g.own + g.TH && r < a.rows) {
+      if (wd == 0 && has_word && i >= g.own && i < g.own + g.TH && r < a.rows) {
         // (one pass does not tell how the image was two passes before)
         const bool moves = a.npasses < 2 || (any != 0u && !periodic);
         const size_t at = size_t(r) * size_t(a.tiles_x) + size_t(g.tx);
@@ -908,9 +910,9 @@ struct DeepArgs {
 };
 
 // Waves per SIMD asked of the register allocator: what LDS lets run.
-template <int BETA>
+template <int BETA, int WAVES>
 constexpr int deep_min_waves() {
-  return BETA <= 2 ? 6 : 4;
+  return WAVES > 8 || BETA > 2 ? 4 : 6;
 }
 
 // With `check`, a workgroup has several tiles, most of them idle: each wave
@@ -939,7 +941,7 @@ __device__ __forceinline__ void walk_tiles(int* runs, int ntiles, int check, Loo
 }
 
 template <int BETA, int WAVES>
-__global__ __launch_bounds__(WAVES * 64, (deep_min_waves<BETA>())) void deep_kernel(DeepArgs a) {
+__global__ __launch_bounds__(WAVES * 64, (deep_min_waves<BETA, WAVES>())) void deep_kernel(DeepArgs a) {
   __shared__ DeepSmem<BETA, WAVES> sm;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -953,7 +955,7 @@ __global__ __launch_bounds__(WAVES * 64, (deep_min_waves<BETA>())) void deep_ker
   auto converged = [&] { return __builtin_amdgcn_ballot_w64(v != 0ull) == 0ull; };
   auto looks = [&](int tile) {
     const DeepGeom g = DeepGeom::of<BETA>(a.t, tile);
-    DeepMap<WAVES * kDeepRows + 2 * BETA> map;
+    DeepMap<kDeepH + 2 * BETA> map;
     const bool runs = map.read(a.t, g, lane);
     if (converged()) return false;
     if (!runs) {
@@ -995,7 +997,7 @@ __device__ __forceinline__ DeepTile deep_tile(const ImageDesc& d) {
 // As deep_kernel, over a table of tiles of many images, each with its own
 // parameters, pass index, pass count and convergence (see multi_pass_kernel).
 template <int BETA, int WAVES>
-__global__ __launch_bounds__(WAVES * 64, (deep_min_waves<BETA>())) void multi_deep_kernel(MultiArgs a) {
+__global__ __launch_bounds__(WAVES * 64, (deep_min_waves<BETA, WAVES>())) void multi_deep_kernel(MultiArgs a) {
   __shared__ DeepSmem<BETA, WAVES> sm;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -1013,7 +1015,7 @@ __global__ __launch_bounds__(WAVES * 64, (deep_min_waves<BETA>())) void multi_de
     if (d.npasses <= 0 || !live(d, ref.tile, lane == 0)) return false;
     const DeepTile dt = deep_tile(d);
     const DeepGeom g = DeepGeom::of<BETA>(dt, ref.tile);
-    DeepMap<WAVES * kDeepRows + 2 * BETA> map;
+    DeepMap<kDeepH + 2 * BETA> map;
     if (map.read(dt, g, lane)) return true;
     const unsigned c = idle_tile<BETA>(dt, g, map, lane, 0, 1);
     if (c != 0u && lane < d.npasses)

@@ -84,7 +84,7 @@ const void* kernel_beta(int shape) {
 }
 
 const void* pass_kernel_ptr(int beta, int shape) {
-  if (is_deep(shape)) return deep_kernel_ptr(beta);
+  if (is_deep(shape)) return deep_kernel_ptr(beta, false);
   switch (beta) {
     case 1: return kernel_beta<1>(shape);
     case 2: return kernel_beta<2>(shape);
@@ -177,14 +177,15 @@ hipError_t launch_pass(int beta, int shape, const PassArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_deep(int beta, int shape, DeepArgs a, hipStream_t s) {
-  const void* k = deep_kernel_ptr(beta);
+  const bool wide = beta < 4 && a.ntiles <= device_cus();
+  const void* k = deep_kernel_ptr(beta, wide);
   int grid = pass_grid(beta, shape, a.ntiles);
   const int full = pass_grid(beta, shape, 0, true) / kListedOversubscription * kDeepOversubscription;
   if (k == nullptr || grid <= 0 || full <= 0) return hipErrorInvalidValue;
   a.check = a.t.map_in != nullptr && grid > full ? 1 : 0;
   if (a.check) grid = full;
   void* args[] = {&a};
-  return hipLaunchKernel(k, dim3(grid), dim3(kDeepWaves * 64), args, 0, s);
+  return hipLaunchKernel(k, dim3(grid), dim3((wide ? kDeepWideWaves : kDeepWaves) * 64), args, 0, s);
 }
 
 }  // namespace
@@ -538,7 +539,7 @@ int enqueue_denoise(const uint8_t* d_in, uint8_t* d_out, const phgrms_params& p,
   f.iterations = iterations;
   // Every block re-derives the iteration count from the count slots; a
   // moved image (rare) is copied grid-stride.
-  const int fblocks = int(std::min<long long>((n / 16 + 255) / 256 + 1, 1024));
+  const int fblocks = int(std::min<long long>((n / 16 + 255) / 256 + 1, 512));
   hipLaunchKernelGGL(finish_kernel, dim3(fblocks), dim3(256), 0, s, f);
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "finish launch");
   return PHGRMS_OK;
