@@ -545,6 +545,53 @@ int enqueue_denoise(const uint8_t* d_in, uint8_t* d_out, const phgrms_params& p,
   return PHGRMS_OK;
 }
 
+// A synchronous call's results in page-locked host memory that the GPU writes
+// directly: one block of kHostSlots slots for the process, made at the first
+// use (129 KiB, kept until the process ends), each held by one call at a
+// time, from any thread.
+constexpr int kHostSlots = 16;
+constexpr int kHostSlotWords = 1 + PHGRMS_K_MAX;   // iteration count, totals
+struct HostSlot {
+  int64_t* words = nullptr;   // null: none free
+  HostSlot() {
+    std::lock_guard<std::mutex> lk(mu());
+    static int64_t* block = [] {
+      void* p = nullptr;
+      if (hipHostMalloc(&p, sizeof(int64_t) * kHostSlots * kHostSlotWords, hipHostMallocPortable) != hipSuccess) {
+        (void)hipGetLastError();
+        p = nullptr;
+      }
+      return static_cast<int64_t*>(p);
+    }();
+    if (block == nullptr) return;
+    for (int i = 0; i < kHostSlots && words == nullptr; ++i)
+      if (!used()[i]) {
+        used()[i] = true;
+        index = i;
+        words = block + size_t(i) * kHostSlotWords;
+      }
+  }
+  ~HostSlot() {
+    if (words == nullptr || index < 0) return;
+    std::lock_guard<std::mutex> lk(mu());
+    used()[index] = false;
+  }
+  void abandon() { index = -1; }   // never handed out again
+  HostSlot(const HostSlot&) = delete;
+  HostSlot& operator=(const HostSlot&) = delete;
+
+ private:
+  int index = -1;
+  static std::mutex& mu() {
+    static std::mutex m;
+    return m;
+  }
+  static bool* used() {
+    static bool u[kHostSlots] = {};
+    return u;
+  }
+};
+
 int set_fused_shape(int beta, int cls, int shape) {
   if (beta < 1 || beta > PHGRMS_BETA_MAX || shape < 0 || shape >= kNumShapes || cls < -1 ||
       cls >= kSizeClasses)
@@ -639,21 +686,34 @@ int phgrms_denoise(const uint8_t* d_in, uint8_t* d_out, phgrms_params p, void* d
   uint8_t* ws = static_cast<uint8_t*>(d_ws);
   auto* counts = reinterpret_cast<unsigned long long*>(ws + l.counts_off);
   auto* changed = reinterpret_cast<unsigned long long*>(ws + l.changed_off);
-  int* iters = reinterpret_cast<int*>(ws + l.state_off);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  rc = enqueue_denoise(d_in, d_out, p, fused_shape(p.beta, (long long)p.rows * p.cols),
-                       ws + l.img_off, counts, changed, iters, ws + l.map_off, s);
-  if (rc != PHGRMS_OK) return rc;
-  hipError_t e;
-  if (h_changed && p.k > 0) {
-    e = hipMemcpyAsync(h_changed, changed, sizeof(int64_t) * size_t(p.k), hipMemcpyDeviceToHost, s);
-    if (e != hipSuccess) return hip_fail(e, "changed read-back");
+  // The finish kernel writes the iteration count and the totals into page-
+  // locked memory; where no slot is free, next to each other in the workspace
+  // (the last of the period-2 stop's slots, which this call does not use, is
+  // right before the totals), from where one copy reads both back.  (128^2,
+  // k 5: 44 us a call with a slot, 53 with one copy, 64 with two.)
+  HostSlot slot;
+  int64_t copy[kHostSlotWords];
+  int64_t* res = slot.words != nullptr ? slot.words : copy;
+  unsigned long long* d_res = reinterpret_cast<unsigned long long*>(slot.words != nullptr ? slot.words
+                                                                   : reinterpret_cast<int64_t*>(changed - 1));
+  rc = enqueue_denoise(d_in, d_out, p, fused_shape(p.beta, (long long)p.rows * p.cols), ws + l.img_off, counts,
+                       d_res + 1, reinterpret_cast<int*>(d_res), ws + l.map_off, s);
+  if (rc != PHGRMS_OK) {
+    slot.abandon();   // what was enqueued may still write
+    return rc;
   }
-  int32_t it = 0;
-  e = hipMemcpyAsync(&it, iters, sizeof(int32_t), hipMemcpyDeviceToHost, s);
-  if (e != hipSuccess) return hip_fail(e, "iterations read-back");
-  if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(e, "stream sync");
-  if (h_iterations) *h_iterations = it;
+  hipError_t e = hipSuccess;
+  if (slot.words == nullptr) {
+    e = hipMemcpyAsync(copy, d_res, sizeof(int64_t) * size_t(1 + (h_changed ? p.k : 0)), hipMemcpyDeviceToHost, s);
+    if (e != hipSuccess) return hip_fail(e, "result read-back");
+  }
+  if ((e = hipStreamSynchronize(s)) != hipSuccess) {
+    slot.abandon();
+    return hip_fail(e, "stream sync");
+  }
+  if (h_changed) std::memcpy(h_changed, res + 1, sizeof(int64_t) * size_t(p.k));
+  if (h_iterations) std::memcpy(h_iterations, res, sizeof(int32_t));
   return PHGRMS_OK;
 }
 
@@ -736,7 +796,7 @@ int phgrms_denoise_plain(const uint8_t* d_in, uint8_t* d_out, phgrms_params p, v
   f.iterations = iters;
   // Every block re-derives the iteration count from the count slots; a
   // moved image (rare) is copied grid-stride.
-  const int fblocks = int(std::min<long long>((n / 16 + 255) / 256 + 1, 1024));
+  const int fblocks = int(std::min<long long>((n / 16 + 255) / 256 + 1, 512));
   hipLaunchKernelGGL(finish_kernel, dim3(fblocks), dim3(256), 0, s, f);
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "finish launch");
   if (h_changed && p.k > 0) {
