@@ -593,21 +593,12 @@ int phgrms_batch_run(phgrms_plan* pl, const uint8_t* d_in, size_t in_bytes, uint
           if (g.deep()) {
             // (the lead launches write no map; the first two launches of a
             // loop write buffers that hold nothing of it yet)
-            const size_t half = pl->map_half[i];
-            uint8_t* words = ws + pl->map_off[i];
-            uint8_t* bytes = words + 2 * sizeof(uint32_t) * half;
-            const size_t in = size_t((j - 1) & 1) * half, out = size_t(j & 1) * half;
-            if (j > g.plan.lead) {
-              x.map_in = words + sizeof(uint32_t) * in;
-              x.cnt_in = bytes + in;
-            }
-            if (j >= g.plan.lead) {
-              x.map_out = words + sizeof(uint32_t) * out;
-              x.cnt_out = bytes + out;
-            }
-            x.depth = tg.T;
-            x.th = tg.TH;
-            x.full_store = j < 2 ? 1 : 0;
+            const size_t half = sizeof(uint32_t) * pl->map_half[i];
+            uint8_t* maps = ws + pl->map_off[i];
+            if (j > g.plan.lead) x.map_in = maps + size_t((j - 1) & 1) * half;
+            if (j >= g.plan.lead) x.map_out = maps + size_t(j & 1) * half;
+            x.seq = j;
+            x.deep = deep_geom(tg.T, tg.TH, j < 2);
           } else if (g.maps && pl->map_half[i] > 0) {
             uint8_t* maps = ws + pl->map_off[i];
             // the first kDenseFirstLaunches launches run the dense kernel
@@ -631,7 +622,7 @@ int phgrms_batch_run(phgrms_plan* pl, const uint8_t* d_in, size_t in_bytes, uint
         f.out = outp;
         f.n = nb;
         f.k = p.k;
-        f.plan = g.plan;
+        f.plan = g.plan.packed();
         f.launches = L;
         fin[i] = f;
       }

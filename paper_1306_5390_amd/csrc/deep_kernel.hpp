@@ -982,15 +982,18 @@ __device__ __forceinline__ DeepTile deep_tile(const ImageDesc& d) {
   t.rows = d.rows;
   t.cols = d.cols;
   t.alpha = d.alpha;
-  t.depth = d.depth;
+  t.depth = d.deep & 255;
   t.npasses = d.npasses;
-  t.th = d.th;
+  t.th = (d.deep >> 8) & 255;
   t.tiles_x = d.tiles_x;
   t.map_in = reinterpret_cast<const uint32_t*>(d.map_in);
   t.map_out = reinterpret_cast<uint32_t*>(d.map_out);
-  t.cnt_in = d.cnt_in;
-  t.cnt_out = d.cnt_out;
-  t.full_store = d.full_store;
+  // the count bytes follow both maps of words
+  const size_t n = size_t(d.rows) * size_t(d.tiles_x), odd = size_t(d.seq & 1);
+  uint8_t* bytes = d.map_out + (2 - odd) * sizeof(uint32_t) * n;
+  t.cnt_in = bytes + (1 - odd) * n;
+  t.cnt_out = bytes + odd * n;
+  t.full_store = (d.deep >> 16) & 1;
   return t;
 }
 

@@ -1066,7 +1066,7 @@ struct ImageDesc {
   int npasses;                   // passes for this image in this launch (0: idle)
   int prev_passes;               // passes of its previous launch (0: none)
   int tiles_x;
-  int full_store;                // deep kernels: see DeepTile
+  int deep;                      // deep kernels: deep_geom()
   int* status;                   // or null: set to 1 if the image had converged before
                                  // this launch (its previous launch had a pass with no
                                  // change), else 0; written by the workgroup of tile 0
@@ -1077,12 +1077,13 @@ struct ImageDesc {
   uint8_t* map_out;
   int seq;
   int tile_base;                 // index of the image's tile 0 in the tile table
-  // deep kernels: maps of words (map_in, map_out) and of count bytes, and the
-  // tile geometry
-  const uint8_t* cnt_in;
-  uint8_t* cnt_out;
-  int depth, th;
 };
+// A deep launch's tile geometry for an image (see DeepTile).  Its change maps
+// are one block of rows * tiles_x entries each: words of even launches, of
+// odd ones, count bytes of even launches, of odd ones (`seq` tells which).
+__host__ __device__ constexpr int deep_geom(int depth, int th, bool full_store) {
+  return depth | th << 8 | (full_store ? 1 << 16 : 0);
+}
 
 // One tile of a multi-image launch: image index and tile index within it.
 struct TileRef {
@@ -1291,6 +1292,19 @@ __device__ __forceinline__ unsigned long long pass_total8(const unsigned long lo
 
 // ---- many-image helpers ----------------------------------------------------------
 
+// Ranges of uint64 to clear, block (., y) for range y.
+struct ZeroDesc {
+  unsigned long long* p;
+  long long n;
+};
+[[maybe_unused]] static __global__ void multi_zero_kernel(const ZeroDesc* d, int nranges) {
+  for (int y = blockIdx.y; y < nranges; y += gridDim.y) {
+    const ZeroDesc r = d[y];
+    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < r.n; i += (long long)gridDim.x * blockDim.x)
+      r.p[i] = 0ull;
+  }
+}
+
 struct CopyDesc {
   const uint8_t* src;
   uint8_t* dst;
@@ -1314,8 +1328,7 @@ struct BatchFinishDesc {
   const uint8_t* buf_odd_from_end;   // the other buffer
   uint8_t* out;
   long long n;
-  int k, launches;
-  LaunchPlan plan;
+  int k, plan, launches, pad;        // plan: LaunchPlan::packed
 };
 
 // grid (X, nimages): per image, the totals, the iteration count, and the
@@ -1336,7 +1349,7 @@ struct BatchFinishDesc {
     __syncthreads();
     const int z = s_first_zero;
     const int iters = (z < f.k) ? z + 1 : f.k;
-    int J = f.plan.launch_of(z) + 1;
+    int J = LaunchPlan::unpacked(f.plan).launch_of(z) + 1;
     if (J > f.launches) J = f.launches;
     if (f.k == 0) J = 0;
     if (blockIdx.x == 0 && threadIdx.x == 0 && f.iterations) *f.iterations = iters;

@@ -48,6 +48,9 @@ struct LaunchPlan {
   __host__ __device__ int start(int j) const {   // first pass of launch j
     return j <= lead ? j : lead + first + (j - lead - 1) * rest;
   }
+  // (no launch has 256 passes; a shape that is not deep has lead 0)
+  __host__ __device__ int packed() const { return lead | first << 8 | rest << 16; }
+  __host__ __device__ static LaunchPlan unpacked(int v) { return LaunchPlan{v & 255, (v >> 8) & 255, (v >> 16) & 255}; }
   __host__ __device__ int launch_of(int pass) const {
     return pass < lead ? pass : pass < lead + first ? lead : lead + 1 + (pass - lead - first) / rest;
   }

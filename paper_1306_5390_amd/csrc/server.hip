@@ -107,6 +107,8 @@ struct Req {
   long long tiles = 0;
   size_t off = 0, bytes = 0;
   unsigned long long* counts = nullptr;
+  uint8_t* maps = nullptr;   // deep shapes: change maps, or null (then every launch tests
+                             // every pixel in its first pass)
   uint8_t* wsimg = nullptr;
   uint8_t* out = nullptr;
   double t_submit = 0, t_done = 0;
@@ -177,6 +179,7 @@ namespace {
 
 // Kernel shape, passes per launch, launches and tiles of a request.
 void set_shape(Req& r, int shape) {
+  if (is_deep(shape) && !deep_fits(r.p)) shape = kDefaultShape;
   r.shape = shape;
   r.T = kShapes[shape].T;
   r.L = ((int64_t)r.p.rows * r.p.cols > 0) ? (r.p.k + r.T - 1) / r.T : 0;
@@ -194,9 +197,17 @@ bool try_admit(phgrms_server* S, Req& r) {
   if (S->active_tiles + r.tiles > (long long)S->tiles_cap) return false;
   if (S->heap.in_use + r.bytes > S->cfg.cap_bytes) return false;
   size_t off = 0;
-  if (!S->heap.alloc(r.bytes, &off)) return false;
+  // A deep shape's change maps, 5 % more, where half of the cap is free and
+  // the arena has the room: they are never what a request waits for.
+  const size_t maps = is_deep(r.shape) && deep_fits(r.p) && r.L > 1
+                          ? up256(2 * (sizeof(uint32_t) + 1) * deep_map_words(r.p.rows, r.p.cols)) : 0;
+  const bool with_maps = maps > 0 && S->heap.in_use + r.bytes + maps <= S->cfg.cap_bytes / 2 &&
+                         S->heap.alloc(r.bytes + maps, &off);
+  if (!with_maps && !S->heap.alloc(r.bytes, &off)) return false;
   r.off = off;
   uint8_t* base = S->arena + off;
+  r.maps = with_maps ? base + r.bytes : nullptr;
+  if (with_maps) r.bytes += maps;
   r.counts = reinterpret_cast<unsigned long long*>(base);
   const size_t cbytes = up256(sizeof(uint64_t) * kCountSlots * size_t(std::max(r.p.k, 1)));
   const size_t n = size_t(std::max<int64_t>((int64_t)r.p.rows * r.p.cols, 1));
@@ -307,7 +318,7 @@ int run_step(phgrms_server* S, std::unique_lock<std::mutex>& lk) {
   const size_t o_imgs = 0;
   const size_t o_fin = up256(o_imgs + ni_all * sizeof(ImageDesc));
   const size_t o_tiles = up256(o_fin + nf_all * sizeof(BatchFinishDesc));
-  const size_t up_bytes = o_tiles + nt_all * sizeof(TileRef);
+  size_t up_bytes = o_tiles + nt_all * sizeof(TileRef);
   if (up_bytes > S->stat_off) {   // cannot happen (see the slot layout); fail loudly if it does
     fail(PHGRMS_EDEVICE, "server step descriptors exceed the slot");
     fail_all(S, PHGRMS_EDEVICE);
@@ -338,9 +349,15 @@ int run_step(phgrms_server* S, std::unique_lock<std::mutex>& lk) {
       x.npasses = std::min(r.T, r.p.k - j * r.T);
       x.prev_passes = j >= 1 ? std::min(r.T, r.p.k - (j - 1) * r.T) : 0;
       x.tiles_x = tg.tiles_x;
-      x.depth = tg.T;
-      x.th = tg.TH;
-      x.full_store = 1;
+      if (is_deep(r.shape)) {
+        x.seq = j;
+        x.deep = deep_geom(tg.T, tg.TH, j < 2 || r.maps == nullptr);
+        if (r.maps != nullptr) {
+          const size_t half = sizeof(uint32_t) * deep_map_words(r.p.rows, r.p.cols);
+          x.map_in = j > 0 ? r.maps + size_t((j - 1) & 1) * half : nullptr;
+          x.map_out = r.maps + size_t(j & 1) * half;
+        }
+      }
       x.status = dstat + ni;
       launched.push_back(id);
       himgs[ni++] = x;
@@ -367,7 +384,7 @@ int run_step(phgrms_server* S, std::unique_lock<std::mutex>& lk) {
     f.out = r.out;
     f.n = (long long)r.p.rows * r.p.cols;
     f.k = r.p.k;
-    f.plan = LaunchPlan{0, r.T, r.T};
+    f.plan = LaunchPlan{0, r.T, r.T}.packed();
     f.launches = r.L;
     hfin[nf++] = f;
     finishing.push_back(id);
@@ -403,12 +420,22 @@ int run_step(phgrms_server* S, std::unique_lock<std::mutex>& lk) {
     const size_t n = size_t((int64_t)r.p.rows * r.p.cols);
     if (r.h_out != nullptr && n > 0) downloads.push_back({r.h_out, r.out, n});
   }
+  // the ranges to clear go up with the tables where there is room: one launch
+  // clears them all
+  const size_t o_zero = up256(up_bytes);
+  const bool zero_once = zero_counts.size() > 1 && o_zero + zero_counts.size() * sizeof(ZeroDesc) <= S->stat_off;
+  if (zero_once) {
+    auto* hz = reinterpret_cast<ZeroDesc*>(h + o_zero);
+    for (size_t z = 0; z < zero_counts.size(); ++z)
+      hz[z] = ZeroDesc{reinterpret_cast<unsigned long long*>(zero_counts[z]), (long long)zero_n[z]};
+    up_bytes = o_zero + zero_counts.size() * sizeof(ZeroDesc);
+  }
   S->slot_busy[slot] = true;
   lk.unlock();
 
   hipError_t e = hipSuccess;
   hipStream_t s = S->stream;
-  for (size_t z = 0; z < zero_counts.size() && e == hipSuccess; ++z) {
+  for (size_t z = 0; z < zero_counts.size() && !zero_once && e == hipSuccess; ++z) {
     hipLaunchKernelGGL(zero_u64_kernel, dim3(int(std::min<size_t>((zero_n[z] + 255) / 256, 256))),
                        dim3(256), 0, s, reinterpret_cast<unsigned long long*>(zero_counts[z]),
                        (long long)zero_n[z]);
@@ -418,6 +445,11 @@ int run_step(phgrms_server* S, std::unique_lock<std::mutex>& lk) {
     e = hipMemcpyAsync(uploads[u].dst, uploads[u].src, uploads[u].n, hipMemcpyHostToDevice, s);
   if (e == hipSuccess && up_bytes > 0)
     e = hipMemcpyAsync(d, h, up_bytes, hipMemcpyHostToDevice, s);
+  if (zero_once && e == hipSuccess) {
+    hipLaunchKernelGGL(multi_zero_kernel, dim3(16, int(std::min<size_t>(zero_counts.size(), 65535))), dim3(256), 0, s,
+                       reinterpret_cast<const ZeroDesc*>(d + o_zero), int(zero_counts.size()));
+    e = hipGetLastError();
+  }
   for (auto& L : launches) {
     if (e != hipSuccess || L.ntiles == 0) continue;
     MultiArgs a;
