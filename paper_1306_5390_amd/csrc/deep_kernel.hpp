@@ -964,7 +964,10 @@ __global__ __launch_bounds__(WAVES * 64, (deep_min_waves<BETA, WAVES>())) void d
     }
     return runs;
   };
-  if (!a.check && converged()) return;
+  if (a.check)
+    __syncthreads();   // the counts are cleared before any wave adds an idle tile's
+  else if (converged())
+    return;
   walk_tiles<WAVES>(sm.runs, a.ntiles, a.check, looks, [&](int tile) { run_deep_tile<BETA, WAVES>(sm, a.t, tile); });
   __syncthreads();
   const int shard = (blockIdx.x % kCountShards) * kCountStride;
