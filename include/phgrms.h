@@ -147,9 +147,9 @@ int phgrms_denoise_noalloc(const uint8_t* d_in, uint8_t* d_out, phgrms_params p,
  *          *d_iterations and its output is the result.  The zero-change stop
  *          still applies.  Other bits: PHGRMS_EINVAL.
  * Every pass before the stop computes what phgrms_denoise computes, so the
- * result equals phgrms_denoise with k = the returned iteration count.  With
- * the flag, one pass runs per kernel launch (the cycle test compares each
- * stored pixel with the image two passes before it).  Other arguments,
+ * result equals phgrms_denoise with k = the returned iteration count.  (The
+ * cycle test compares each pixel that may have moved with the image two passes
+ * before, in the launches of the pass loop itself.)  Other arguments,
  * workspace size and results as phgrms_denoise_async; flags = 0 is
  * phgrms_denoise_async. */
 int phgrms_denoise_ex(const uint8_t* d_in, uint8_t* d_out, phgrms_params p,

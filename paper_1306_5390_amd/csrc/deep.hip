@@ -9,19 +9,23 @@
 
 namespace phg {
 
-template <int WAVES>
+template <int WAVES, bool CYC>
 static const void* deep_ptr(int beta) {
   switch (beta) {
-    case 1: return reinterpret_cast<const void*>(&deep_kernel<1, WAVES>);
-    case 2: return reinterpret_cast<const void*>(&deep_kernel<2, WAVES>);
-    case 3: return reinterpret_cast<const void*>(&deep_kernel<3, WAVES>);
-    case 4: return reinterpret_cast<const void*>(&deep_kernel<4, kDeepWaves>);
+    case 1: return reinterpret_cast<const void*>(&deep_kernel<1, WAVES, CYC>);
+    case 2: return reinterpret_cast<const void*>(&deep_kernel<2, WAVES, CYC>);
+    case 3: return reinterpret_cast<const void*>(&deep_kernel<3, WAVES, CYC>);
+    case 4: return reinterpret_cast<const void*>(&deep_kernel<4, kDeepWaves, CYC>);
     default: return nullptr;
   }
 }
 
 const void* deep_kernel_ptr(int beta, bool wide) {
-  return wide ? deep_ptr<kDeepWideWaves>(beta) : deep_ptr<kDeepWaves>(beta);
+  return wide ? deep_ptr<kDeepWideWaves, false>(beta) : deep_ptr<kDeepWaves, false>(beta);
+}
+
+const void* deep_cycle_ptr(int beta, bool wide) {
+  return wide ? deep_ptr<kDeepWideWaves, true>(beta) : deep_ptr<kDeepWaves, true>(beta);
 }
 
 const void* multi_deep_ptr(int beta) {

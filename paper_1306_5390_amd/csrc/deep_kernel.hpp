@@ -64,6 +64,8 @@ struct DeepTile {
   int rows, cols, alpha;
   int depth;                 // passes the tile geometry is laid out for
   int npasses;               // passes to run, 1..depth
+  int advance;               // passes after which the stored image and the map are taken (period-2
+                             // launches; else npasses)
   int th;                    // owned rows of a tile
   int tiles_x;
   const uint32_t* map_in;    // change map of the previous launch, or null: the first pass
@@ -200,7 +202,7 @@ struct DeepMap {
     // Where no pixel in reach differs from two passes before, the region
     // goes on alternating between its last two images, and an even number
     // of passes ends where it began.
-    return __builtin_amdgcn_ballot_w64((a.npasses & 1 ? groups : moves) != 0u) != 0ull;
+    return __builtin_amdgcn_ballot_w64((a.advance & 1 ? groups : moves) != 0u) != 0ull;
   }
   __device__ __forceinline__ bool row_stale(int lr) const {
     return ((stale[NCH > 1 && lr >= 64 ? NCH - 1 : 0] >> (lr & 63)) & 1ull) != 0ull;
@@ -475,7 +477,8 @@ __device__ __forceinline__ void push_candidates(uint32_t cand, uint32_t ent, uin
 // The band test on every pixel of R computed rows from `strip` on, as in
 // pass_kernel.hpp.  Candidates go to the ring q (through dq) and to
 // evaluate(valid, LDS row << 8 | column) in rounds of 64; those left over are
-// entries [qhead, qtail) of q.  row(LDS row, lane's dword) takes every row.
+// entries [qhead, qtail) of q.  row(LDS row, lane's dword, candidates, pixels
+// that the pass must get right) takes every row.
 template <int BETA, int R, class Eval, class Row>
 __device__ __forceinline__ void dense_rows(const uint32_t* src, int strip, int lane, const DeepBounds& b,
                                            const Band& band, uint16_t* q, uint32_t* dq, int& qhead,
@@ -519,7 +522,8 @@ __device__ __forceinline__ void dense_rows(const uint32_t* src, int strip, int l
         const int i = strip + jc;
         const uint32_t X = win[(jj + BETA) % NW][BETA];
         const bool test = i >= b.row_lo && i < b.row_hi;
-        uint32_t cand = test ? colmask : 0u;
+        const uint32_t tested = test ? colmask : 0u;
+        uint32_t cand = tested;
         if (test && band.alpha > 0) {
           const uint32_t nx = ~X;
           const uint32_t nlo = sat_add_u8x4(nx, band.am1_16);
@@ -558,7 +562,7 @@ __device__ __forceinline__ void dense_rows(const uint32_t* src, int strip, int l
             }
           }
         }
-        row(i + BETA, X);
+        row(i + BETA, X, cand, tested);
         const unsigned long long hb = __builtin_amdgcn_ballot_w64(cand != 0u);
         if (hb != 0ull) {
           const int pos = dtail + bits_below(hb);
@@ -615,6 +619,8 @@ struct DeepSmem {
   unsigned fill;                    // entries of a list built from the change bits
   unsigned moves[3];                // the same of: a pixel became other than two passes before
   unsigned count[kDeepMaxPasses];   // owned pixels each pass changed
+  unsigned moved[kDeepMaxPasses];   // (period-2 launches) whether a pass left a pixel other than two
+                                    // passes before; over the tiles of the workgroup
   unsigned row_any[(BROWS + 31) / 32];               // LDS rows changed before list passes
   unsigned changed[kDeepMaxPasses];
 };
@@ -648,7 +654,7 @@ __device__ __forceinline__ unsigned idle_tile(const DeepTile& a, const DeepGeom&
 // Run the tile's passes and add its per-pass changed counts to sm.changed
 // (threads 0 .. npasses - 1, one pass each).  Called by every thread of the
 // workgroup.
-template <int BETA, int WAVES>
+template <int BETA, int WAVES, bool CYC = false>
 __device__ __forceinline__ void run_deep_tile(DeepSmem<BETA, WAVES>& sm, const DeepTile& a, int tile) {
   constexpr int NW = 2 * BETA + 1;
   constexpr int N = NW * NW;
@@ -761,11 +767,12 @@ __device__ __forceinline__ void run_deep_tile(DeepSmem<BETA, WAVES>& sm, const D
         __syncthreads();
         if (tid == 0) sm.fill = 0u;
       }
-      // chg[cb] is cleared behind the list for the pass after this
+      // chg[cb] is cleared behind the list for the pass after this (not where
+      // the map is taken before the last pass)
       if (!groups && tid < int(n)) {
         const unsigned e = list[tid];
         const int lr = int(e >> 8);
-        cur[lr * 8 + (int(e & 255u) >> 5)] = 0u;
+        if (!CYC || t + 1 < a.npasses || a.advance == a.npasses) cur[lr * 8 + (int(e & 255u) >> 5)] = 0u;
         atomicOr(&sm.row_any[lr >> 5], 1u << (lr & 31));
       }
       const int span = groups ? NW + 7 : NW;       // window columns of an entry
@@ -814,8 +821,18 @@ __device__ __forceinline__ void run_deep_tile(DeepSmem<BETA, WAVES>& sm, const D
         const int words = all ? kDeepWords + 1 : queue_words(has_word ? active_word<BETA>(cur, strip, ri, wd, b) : 0u, wq, ri, wd);
         if (words > kDeepWords) {
           dense_rows<BETA, R>(src, strip, lane, b, band, q, sm.lanes[w], qhead, qtail, evaluate,
-                           [&](int lr, uint32_t X) { dst[lr * kRowWords + 1 + lane] = X; });
-          moved = true;                            // (not looked at)
+                           [&](int lr, uint32_t X, uint32_t cand, uint32_t tested) {
+                             uint32_t* d = dst + lr * kRowWords + 1 + lane;
+                             if constexpr (CYC) {
+                               // candidates keep the destination's byte until they are evaluated
+                               const uint32_t x = (X ^ *d) & ~((cand >> 7) * 255u);
+                               moved = moved || (x & ((tested >> 7) * 255u)) != 0u;
+                               *d ^= x;
+                             } else {
+                               *d = X;
+                             }
+                           });
+          if (!CYC) moved = true;                  // (not looked at)
         } else {
           for (int m0 = 0; m0 < words; m0 += 64) {
             uint32_t cand = 0u, ent = 0u;
@@ -835,7 +852,15 @@ __device__ __forceinline__ void run_deep_tile(DeepSmem<BETA, WAVES>& sm, const D
               if (other != 0u) {
                 const uint32_t full = (other >> 7) * 255u;
                 *d = (*d & ~full) | (X & full);
-                moved = true;
+                // (beside the region that this pass must get right, what the
+                // destination holds says nothing)
+                bool counts = !CYC;
+                if constexpr (CYC) {
+#pragma unroll
+                  for (int k = 0; k < 4; ++k)
+                    counts = counts || (((other >> (8 * k + 7)) & 1u) != 0u && 4 * wi + k >= b.col_lo && 4 * wi + k < b.col_hi);
+                }
+                moved = moved || counts;
               }
             }
             push_candidates(cand, ent, q, qtail);
@@ -852,7 +877,10 @@ __device__ __forceinline__ void run_deep_tile(DeepSmem<BETA, WAVES>& sm, const D
     }
     groups = false;
     if (lane == 0 && wave_changed != 0u) atomicAdd(&sm.count[t], wave_changed);
-    if (__builtin_amdgcn_ballot_w64(moved) != 0ull && lane == 0) sm.moves[(t + 1) % 3] = 1u;
+    if (__builtin_amdgcn_ballot_w64(moved) != 0ull && lane == 0) {
+      sm.moves[(t + 1) % 3] = 1u;
+      if (CYC) sm.moved[t] = 1u;
+    }
     __syncthreads();
     uint32_t* tmp = src;
     src = dst;
@@ -860,7 +888,9 @@ __device__ __forceinline__ void run_deep_tile(DeepSmem<BETA, WAVES>& sm, const D
     cb ^= 1;
   }
   // (a tile that alternates ends in the other buffer after an odd number of passes)
-  if ((a.npasses - t) & 1) src = dst;
+  if ((a.advance - t) & 1) src = dst;
+  // the map's changes: those before the last pass, where the image is taken before it
+  if (CYC && t == a.npasses && a.advance < t) cb ^= 1;
   if (tid < a.npasses) sm.changed[tid] += sm.count[tid < t ? tid : max(t - 1, 0)];
 
   // The strip's map words and owned rows.
@@ -878,7 +908,7 @@ __device__ __forceinline__ void run_deep_tile(DeepSmem<BETA, WAVES>& sm, const D
       const int r = g.row_first + BETA + i;
       if (wd == 0 && has_word && i >= g.own && i < g.own + g.TH && r < a.rows) {
         // (one pass does not tell how the image was two passes before)
-        const bool moves = a.npasses < 2 || (any != 0u && !periodic);
+        const bool moves = a.advance < 2 || (any != 0u && !periodic);
         const size_t at = size_t(r) * size_t(a.tiles_x) + size_t(g.tx);
         a.map_out[at] = word | (any != 0u ? kMapAny : 0u) | (moves ? kMapMoves : 0u);
         a.cnt_out[at] = uint8_t(c);
@@ -907,6 +937,16 @@ struct DeepArgs {
   int pass0;                     // index of this launch's first pass
   int ntiles;
   int check;                     // 1: a workgroup looks at several tiles at once
+  // Period-2 launches: the slots of the passes that moved a pixel (as
+  // `changed`; pass 0's say nothing).  The first pass of every launch but the
+  // first is the last one of the launch before, which says what its second
+  // pass is compared with: it is not counted again.
+  unsigned long long* diff2;
+  // Or, where fix is not null, the one pass that may be missing after the stop
+  // (see CyclePlan): run unless *fix is negative, with source and destination,
+  // and the two maps, exchanged where it is odd.
+  const int* fix;
+  const uint32_t* fix_map1;
 };
 
 // Waves per SIMD asked of the register allocator: what LDS lets run.
@@ -940,19 +980,34 @@ __device__ __forceinline__ void walk_tiles(int* runs, int ntiles, int check, Loo
   }
 }
 
-template <int BETA, int WAVES>
+template <int BETA, int WAVES, bool CYC = false>
 __global__ __launch_bounds__(WAVES * 64, (deep_min_waves<BETA, WAVES>())) void deep_kernel(DeepArgs a) {
   __shared__ DeepSmem<BETA, WAVES> sm;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  if (tid < kDeepMaxPasses) sm.changed[tid] = 0u;
+  if (tid < kDeepMaxPasses) sm.changed[tid] = sm.moved[tid] = 0u;
+  if (CYC && a.fix != nullptr) {
+    const int f = __builtin_amdgcn_readfirstlane(*a.fix);
+    if (f < 0) return;
+    const uint8_t* const s = a.t.src;
+    uint8_t* const d = a.t.dst;
+    a.t.map_in = f & 1 ? a.fix_map1 : a.t.map_in;
+    a.t.src = f & 1 ? d : s;
+    a.t.dst = f & 1 ? const_cast<uint8_t*>(s) : d;
+  }
   // After a pass without a change the image is a fixed point, and so every
   // later pass has no change either: the last pass of the previous launch
   // tells (a launch that does not run leaves its counts at zero).  The load
   // of the vote is in flight with those of the map words.
-  const unsigned long long v = a.pass0 <= 0 ? 1ull : lane < kCountShards
-      ? a.changed[(a.pass0 - 1) * kCountSlots + lane * kCountStride] : 0ull;
-  auto converged = [&] { return __builtin_amdgcn_ballot_w64(v != 0ull) == 0ull; };
+  // (Period-2 launches: the pass that this launch does again; and a pass that
+  // moved nothing ends the run too.)
+  const int vp = CYC ? a.pass0 : a.pass0 - 1;
+  const int vs = vp * kCountSlots + lane * kCountStride;
+  const unsigned long long v = a.pass0 <= 0 ? 1ull : lane < kCountShards ? a.changed[vs] : 0ull;
+  const unsigned long long v2 = !CYC || a.pass0 <= 0 ? 1ull : lane < kCountShards ? a.diff2[vs] : 0ull;
+  auto converged = [&] {
+    return __builtin_amdgcn_ballot_w64(v != 0ull) == 0ull || __builtin_amdgcn_ballot_w64(v2 != 0ull) == 0ull;
+  };
   auto looks = [&](int tile) {
     const DeepGeom g = DeepGeom::of<BETA>(a.t, tile);
     DeepMap<kDeepH + 2 * BETA> map;
@@ -968,9 +1023,13 @@ __global__ __launch_bounds__(WAVES * 64, (deep_min_waves<BETA, WAVES>())) void d
     __syncthreads();   // the counts are cleared before any wave adds an idle tile's
   else if (converged())
     return;
-  walk_tiles<WAVES>(sm.runs, a.ntiles, a.check, looks, [&](int tile) { run_deep_tile<BETA, WAVES>(sm, a.t, tile); });
+  walk_tiles<WAVES>(sm.runs, a.ntiles, a.check, looks, [&](int tile) { run_deep_tile<BETA, WAVES, CYC>(sm, a.t, tile); });
   __syncthreads();
+  if (CYC && a.fix != nullptr) return;             // (its counts are not wanted)
   const int shard = (blockIdx.x % kCountShards) * kCountStride;
+  if (CYC && tid == 0 && a.pass0 > 0) return;      // (counted by the launch before)
+  if (CYC && tid < a.t.npasses && sm.moved[tid] != 0u)
+    atomicAdd(a.diff2 + (a.pass0 + tid) * kCountSlots + shard, 1ull);
   if (tid < a.t.npasses && sm.changed[tid] != 0u)
     atomicAdd(a.changed + (a.pass0 + tid) * kCountSlots + shard, (unsigned long long)sm.changed[tid]);
 }
@@ -986,7 +1045,7 @@ __device__ __forceinline__ DeepTile deep_tile(const ImageDesc& d) {
   t.cols = d.cols;
   t.alpha = d.alpha;
   t.depth = d.deep & 255;
-  t.npasses = d.npasses;
+  t.npasses = t.advance = d.npasses;
   t.th = (d.deep >> 8) & 255;
   t.tiles_x = d.tiles_x;
   t.map_in = reinterpret_cast<const uint32_t*>(d.map_in);

@@ -1290,6 +1290,55 @@ __device__ __forceinline__ unsigned long long pass_total8(const unsigned long lo
   copy_range(fin, f.out, f.n);
 }
 
+struct CycleFinishArgs {
+  const unsigned long long* counts;
+  const unsigned long long* diff2;   // nonzero where a pass moved a pixel
+  unsigned long long* changed;       // out: per-pass totals, k entries
+  int* iterations;
+  int* state;                        // out: [0] -1, or the parity of the last launch that ran, if its
+                                     // buffer does not hold the result; [1] the parity of the launches
+                                     // whose buffer does (after the pass that [0] asks for)
+  CyclePlan plan;
+  int launches;
+};
+
+// One block: the totals, the passes run, and where the result is.  Passes
+// after the stop count as not run.
+[[maybe_unused]] static __global__ __launch_bounds__(256) void cycle_plan_kernel(CycleFinishArgs f) {
+  __shared__ int s_stop, s_fixed;
+  if (threadIdx.x == 0) s_stop = s_fixed = f.plan.k;
+  __syncthreads();
+  const int part = threadIdx.x & 7;
+  for (int t = threadIdx.x >> 3; t < f.plan.k; t += 32) {
+    const unsigned long long tot = pass_total8(f.counts, t, part);
+    const bool still = t >= 1 && pass_total8(f.diff2, t, part) == 0ull;
+    if (part == 0) f.changed[t] = tot;
+    if (part == 0 && tot == 0ull) atomicMin(&s_fixed, t);
+    if (part == 0 && (tot == 0ull || still)) atomicMin(&s_stop, t);
+  }
+  __syncthreads();
+  const int z = s_stop;
+  for (int t = z + 1 + int(threadIdx.x); t < f.plan.k; t += blockDim.x) f.changed[t] = 0ull;
+  if (threadIdx.x != 0) return;
+  *f.iterations = z < f.plan.k ? z + 1 : f.plan.k;
+  // launch j ran unless the stop came by the pass it begins with
+  int j = 0;
+  while (j + 1 < f.launches && f.plan.start(j + 1) < z) ++j;
+  // its buffer holds the image after `at` passes; from z passes on the image
+  // alternates (or, after a pass without a change, stays)
+  const int at = f.plan.start(j) + f.plan.advance(j);
+  const bool fix = z < f.plan.k && s_fixed != z && ((at - (z + 1)) & 1) != 0;
+  f.state[0] = fix ? j & 1 : -1;
+  f.state[1] = (j ^ (fix ? 1 : 0)) & 1;
+}
+
+// Move the result to `out` if it is in the workspace image: launches of
+// parity `out_parity` write `out`.
+[[maybe_unused]] static __global__ void cycle_copy_kernel(const int* state, int out_parity, const uint8_t* ws,
+                                                          uint8_t* out, long long n) {
+  if (state[1] != out_parity) copy_range(ws, out, n);
+}
+
 // ---- many-image helpers ----------------------------------------------------------
 
 // Ranges of uint64 to clear, block (., y) for range y.

@@ -176,9 +176,9 @@ hipError_t launch_pass(int beta, int shape, const PassArgs& a, hipStream_t s) {
   return hipLaunchKernel(k, dim3(grid), dim3(kShapes[shape].waves * 64), args, 0, s);
 }
 
-hipError_t launch_deep(int beta, int shape, DeepArgs a, hipStream_t s) {
+hipError_t launch_deep(int beta, int shape, DeepArgs a, hipStream_t s, bool cycle = false) {
   const bool wide = beta < 4 && a.ntiles <= device_cus();
-  const void* k = deep_kernel_ptr(beta, wide);
+  const void* k = cycle ? deep_cycle_ptr(beta, wide) : deep_kernel_ptr(beta, wide);
   int grid = pass_grid(beta, shape, a.ntiles);
   const int full = pass_grid(beta, shape, 0, true) / kListedOversubscription * kDeepOversubscription;
   if (k == nullptr || grid <= 0 || full <= 0) return hipErrorInvalidValue;
@@ -470,13 +470,15 @@ int enqueue_denoise(const uint8_t* d_in, uint8_t* d_out, const phgrms_params& p,
         // loop write buffers that hold nothing of it yet)
         const bool has_map = deep_maps && j > plan.lead;
         DeepArgs a;
-        a.t = DeepTile{src, dst_of(j), p.rows, p.cols, p.alpha, depth, depth, gd.TH, gd.tiles_x,
+        a.t = DeepTile{src, dst_of(j), p.rows, p.cols, p.alpha, depth, depth, depth, gd.TH, gd.tiles_x,
                        has_map ? words + in : nullptr, deep_maps ? words + out : nullptr,
                        has_map ? bytes + in : nullptr, deep_maps ? bytes + out : nullptr, j < 2 ? 1 : 0};
         a.changed = counts;
         a.pass0 = start;
         a.ntiles = int(gd.ntiles);
         a.check = 0;
+        a.diff2 = nullptr;
+        a.fix = nullptr;
         if ((e = launch_deep(p.beta, shape, a, s)) != hipSuccess) return hip_fail(e, "pass launch");
         src = a.t.dst;
         continue;
@@ -541,6 +543,114 @@ int enqueue_denoise(const uint8_t* d_in, uint8_t* d_out, const phgrms_params& p,
   // moved image (rare) is copied grid-stride.
   const int fblocks = int(std::min<long long>((n / 16 + 255) / 256 + 1, 512));
   hipLaunchKernelGGL(finish_kernel, dim3(fblocks), dim3(256), 0, s, f);
+  if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "finish launch");
+  return PHGRMS_OK;
+}
+
+// Launches after the first run an odd number of passes: their stored image is
+// an even number of passes on, so that tiles that alternate are idle.  Large
+// images have the shorter first launch: its passes test every pixel of the
+// halo too (k 20, us per call, with the longer first launch and with the
+// shorter: 8192^2: 1062 and 877 at beta 1, 719 and 648 at beta 2, 431 and 386
+// at beta 3; 2048^2: 131 and 116, 92 and 79, 64 and 64; but 1023 x 1537, k 8,
+// beta 2: 44 and 52).
+static CyclePlan cycle_plan(const phgrms_params& p) {
+  const bool large = (int64_t)p.rows * p.cols >= (int64_t(1) << 22);
+  return p.beta == 1   ? CyclePlan{p.k, large ? 8 : 16, 15}
+         : p.beta == 2 ? CyclePlan{p.k, large ? 6 : 8, 7}
+         : p.beta == 3 ? CyclePlan{p.k, large ? 3 : 4, 5} : CyclePlan{p.k, 4, 3};
+}
+
+// Whether the period-2 stop runs by deep launches: where their change maps
+// fit, and the one-pass launches are not as fast.  Those are, with their
+// smaller halo and a finish of one launch, for the first few passes of a large
+// image whose rows start on dword boundaries, and more so at the larger betas
+// (us per call, one-pass and deep, a tenth of the pixels noise or, at beta 1,
+// four tenths; 512^2, beta 1, k 2: 21 and 23; 4096^2: beta 1, k 4: 103 and
+// 120, k 6: 145 and 147, a tenth noise 118 and 81; beta 2, k 3: 106 and 110,
+// k 4: 144 and 120; beta 3, k 6: 239 and 278, k 10: 392 and 349; 2048^2, beta
+// 4, k 6: 122 and 148, k 10: 199 and 183; 8192^2, beta 1, k 10: 667 and 691,
+// k 12: 786 and 739).  At beta 4 large images are faster by the one or by the
+// other, as their noise is (4096^2, k 32: 905 and 674, four tenths noise 193
+// and 296), and stay with the one-pass launches.
+static bool deep_cycle(const phgrms_params& p) {
+  const int64_t n = (int64_t)p.rows * p.cols;
+  if (p.k <= 1 || n <= 0 || !deep_fits(p) ||
+      2 * (sizeof(uint32_t) + 1) * deep_map_words(p.rows, p.cols) > change_map_bytes(p.rows, p.cols))
+    return false;
+  const bool huge = n >= (int64_t(1) << 25);
+  if ((p.cols & 3) != 0) return p.beta < 4 || !huge;
+  if (n < (int64_t(1) << 21)) return p.k > 2 || n < (int64_t(1) << 18);
+  switch (p.beta) {
+    case 1: return p.k > (huge ? 10 : 4);
+    case 2: return p.k > 3;
+    case 3: return p.k > 8;
+    default: return p.k > 8 && n < (int64_t(1) << 23);
+  }
+}
+
+// As enqueue_denoise, with the period-2 stop, by deep launches (CyclePlan).
+// The launch that comes to the stop runs its other passes too: nothing moves
+// any more, so a tile only counts them.  The image then alternates, so what
+// that launch stored is the result or the image before it, and in the latter
+// case one more pass makes the result.  1023 x 1537, beta 2, k 32: 81 us, 312
+// by one-pass launches.
+int enqueue_deep_cycle(const uint8_t* d_in, uint8_t* d_out, const phgrms_params& p, int shape, uint8_t* ws_img,
+                       unsigned long long* counts, unsigned long long* changed, int* iterations, int* state,
+                       uint8_t* maps, hipStream_t s) {
+  const long long n = (long long)p.rows * p.cols;
+  unsigned long long* diff2 = counts + (long long)p.k * kCountSlots;   // (WsLayout: right after them)
+  hipError_t e;
+  const long long nc = 2ll * p.k * kCountSlots;
+  hipLaunchKernelGGL(zero_u64_kernel, dim3(int(std::min<long long>((nc + 255) / 256, 1024))), dim3(256), 0, s, counts,
+                     nc);
+  if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "init launch");
+  const CyclePlan plan = cycle_plan(p);
+  int L = 1;
+  while (!plan.last(L - 1)) ++L;
+  auto dst_of = [&](int j) -> uint8_t* { return ((L - 1 - j) % 2 == 0) ? d_out : ws_img; };
+  const uint8_t* src = d_in;
+  if (d_in == d_out && dst_of(0) == d_out) {
+    // Launch 0 must not write the buffer it reads: stage the input first.
+    const int blocks = int(std::min<long long>((n / 4 + 255) / 256 + 1, 4096));
+    hipLaunchKernelGGL(copy_bytes_kernel, dim3(blocks), dim3(256), 0, s, d_in, ws_img, n);
+    if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "stage launch");
+    src = ws_img;
+  }
+  const size_t M = deep_map_words(p.rows, p.cols);
+  uint32_t* const words = reinterpret_cast<uint32_t*>(maps);
+  uint8_t* const bytes = maps + 2 * sizeof(uint32_t) * M;
+  DeepArgs a;
+  a.changed = counts;
+  a.diff2 = diff2;
+  a.check = 0;
+  a.fix = nullptr;
+  for (int j = 0; j < L; ++j) {
+    const int np = plan.passes(j);
+    const TileGeom g = tile_geom(p, shape, np, true);
+    const size_t in = size_t((j - 1) & 1) * M, out = size_t(j & 1) * M;
+    a.t = DeepTile{src, dst_of(j), p.rows, p.cols, p.alpha, np, np, plan.advance(j), g.TH, g.tiles_x,
+                   j > 0 ? words + in : nullptr, words + out, j > 0 ? bytes + in : nullptr, bytes + out, j < 2 ? 1 : 0};
+    a.pass0 = plan.start(j);
+    a.ntiles = int(g.ntiles);
+    if ((e = launch_deep(p.beta, shape, a, s, true)) != hipSuccess) return hip_fail(e, "pass launch");
+    src = a.t.dst;
+  }
+  CycleFinishArgs f{counts, diff2, changed, iterations, state, plan, L};
+  hipLaunchKernelGGL(cycle_plan_kernel, dim3(1), dim3(256), 0, s, f);
+  if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "finish launch");
+  // The pass after the stop: from the last launch's buffer to the other one.
+  // (state[0]: -1 or the parity of that launch; launch j wrote map j & 1 and
+  // dst_of(j).)
+  const TileGeom g1 = tile_geom(p, shape, 1, true);
+  a.t = DeepTile{dst_of(0), dst_of(1), p.rows, p.cols, p.alpha, 1, 1, 1, g1.TH, g1.tiles_x, words, nullptr, bytes, nullptr, 1};
+  a.pass0 = 0;
+  a.ntiles = int(g1.ntiles);
+  a.fix = state;
+  a.fix_map1 = words + M;
+  if ((e = launch_deep(p.beta, shape, a, s, true)) != hipSuccess) return hip_fail(e, "pass launch");
+  const int fblocks = int(std::min<long long>((n / 16 + 255) / 256 + 1, 512));
+  hipLaunchKernelGGL(cycle_copy_kernel, dim3(fblocks), dim3(256), 0, s, state, (L - 1) & 1, ws_img, d_out, n);
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "finish launch");
   return PHGRMS_OK;
 }
@@ -666,8 +776,12 @@ int phgrms_denoise_ex(const uint8_t* d_in, uint8_t* d_out, phgrms_params p, int3
                             : reinterpret_cast<int*>(ws + l.state_off);
   int shape = fused_shape(p.beta, (long long)p.rows * p.cols);
   unsigned long long* diff2 = nullptr;
+  if ((flags & PHGRMS_STOP_ON_CYCLE) && is_deep(shape) && deep_cycle(p))
+    return enqueue_deep_cycle(d_in, d_out, p, shape, ws + l.img_off, counts, changed, iters,
+                              reinterpret_cast<int*>(ws + l.state_off) + 16, ws + l.map_off,
+                              static_cast<hipStream_t>(stream));
   if (flags & PHGRMS_STOP_ON_CYCLE) {
-    // the period-2 variants: the tuned skipping shape's own, else (1, 8, 4)
+    // by one-pass launches, the period-2 variants: the tuned skipping shape's own, else (1, 8, 4)
     // with change tracking if the tuned shape tracks changes, else without
     diff2 = reinterpret_cast<unsigned long long*>(ws + l.diff_off);
     if (is_deep(shape)) shape = one_pass_shape(p.beta, (long long)p.rows * p.cols, true);
@@ -842,12 +956,14 @@ int phgrms_run_passes(const uint8_t* d_src, uint8_t* d_dst, phgrms_params p, int
   if (is_deep(shape)) {
     if (!deep_fits(p)) return fail(PHGRMS_EUNSUPPORTED, "shape %d needs sides below 2^30", shape);
     DeepArgs a;
-    a.t = DeepTile{d_src, d_dst, p.rows, p.cols, p.alpha, p.k, p.k, g.TH, g.tiles_x, nullptr,
+    a.t = DeepTile{d_src, d_dst, p.rows, p.cols, p.alpha, p.k, p.k, p.k, g.TH, g.tiles_x, nullptr,
                    nullptr, nullptr, nullptr, 1};
     a.changed = reinterpret_cast<unsigned long long*>(d_changed);
     a.pass0 = 0;
     a.ntiles = int(g.ntiles);
     a.check = 0;
+    a.diff2 = nullptr;
+    a.fix = nullptr;
     const hipError_t ed = launch_deep(p.beta, shape, a, static_cast<hipStream_t>(stream));
     return ed == hipSuccess ? PHGRMS_OK : hip_fail(ed, "pass launch");
   }

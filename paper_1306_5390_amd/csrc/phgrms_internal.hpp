@@ -16,6 +16,23 @@ constexpr int kDefaultShape = 3;   // (1, 8, 4): one pass, 8 rows per wave, 4 wa
 // kernel of kDefaultShape (no change maps).  At most 2: the list-building
 // launch of a skipping shape is launch 2.
 constexpr int kDenseFirstLaunches = 2;
+// The launches of a deep loop with the period-2 stop: a pass can be compared
+// with the image two passes before only if the launch has that one, so every
+// launch but the first begins with the last pass of the launch before, which
+// stores the image as it was before that pass (the last launch: after it).
+// `first` passes in launch 0, `rest` in the others.
+struct CyclePlan {
+  int k, first, rest;
+  __host__ __device__ int start(int j) const { return j == 0 ? 0 : first - 1 + (j - 1) * (rest - 1); }
+  __host__ __device__ int passes(int j) const {
+    const int n = j == 0 ? first : rest, left = k - start(j);
+    return n < left ? n : left;
+  }
+  __host__ __device__ bool last(int j) const { return start(j) + passes(j) >= k; }
+  // passes after which launch j's stored image is taken
+  __host__ __device__ int advance(int j) const { return last(j) ? passes(j) : passes(j) - 1; }
+};
+
 // Workgroups of a launch over listed tiles, in multiples of the grid that
 // fits on the device at once.
 constexpr int kListedOversubscription = 4;
@@ -100,6 +117,7 @@ inline bool is_deep(int shape) { return kShapes[shape].track == 3; }
 constexpr int kDeepWaves = 8;      // waves of a workgroup
 constexpr int kDeepWideWaves = 16; // the same where no CU has more than one (beta 1 .. 3)
 const void* deep_kernel_ptr(int beta, bool wide);
+const void* deep_cycle_ptr(int beta, bool wide);   // the period-2 variant
 const void* multi_deep_ptr(int beta);
 // A tile's row and column arithmetic stays inside an int.
 bool deep_fits(const phgrms_params& p);

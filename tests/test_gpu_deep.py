@@ -29,7 +29,7 @@ def _oscillating(rows, cols, seed):
     return np.clip(img, 0, 255).astype(np.uint8)
 
 
-def _run(img, alpha, beta, k, shape=DEEP, offset=0, in_place=False):
+def _run(img, alpha, beta, k, shape=DEEP, offset=0, in_place=False, cycle=False):
     torch, m = _modules()
     rows, cols = img.shape
     cls = m.size_class(rows * cols)
@@ -42,14 +42,14 @@ def _run(img, alpha, beta, k, shape=DEEP, offset=0, in_place=False):
         out = src if in_place else torch.full((rows, cols), 77, dtype=torch.uint8, device="cuda:0")
         ws = torch.full((m.workspace_bytes(rows, cols, alpha, beta, k),), 0xA5, dtype=torch.uint8,
                         device="cuda:0")
-        got, ch, it = m.denoise_async(src, alpha, beta, k, out=out, workspace=ws)
+        got, ch, it = m.denoise_async(src, alpha, beta, k, out=out, workspace=ws, stop_on_cycle=cycle)
         return got.cpu().numpy(), int(it.item()), ch.cpu().tolist()
     finally:
         m.set_tuning_class(beta, cls, saved)
 
 
 def _check(img, alpha, beta, k, **kw):
-    ref, rit, rch = oracle.denoise(img, alpha, beta, k)
+    ref, rit, rch = (oracle.denoise_cycle if kw.get("cycle") else oracle.denoise)(img, alpha, beta, k)
     got, it, ch = _run(img, alpha, beta, k, **kw)
     assert np.array_equal(got, ref), (img.shape, alpha, beta, k, kw)
     assert it == rit and ch[:it] == list(rch)[:rit] and not any(ch[it:]), (it, rit, ch, rch)
@@ -158,3 +158,40 @@ def test_served_requests(passes):
             srv.release(rid)
     assert not todo
     srv.close()
+
+
+# _oscillating(40, 200, seed) stops with pass `last`: around the first pass of
+# the second launch (15 at beta 1, 7 at beta 2, 3 at beta 3), which that launch
+# runs again to have the image two passes before its next one.
+@pytest.mark.parametrize("beta,alpha,seed,last", [(1, 6, 4, 14), (1, 6, 26, 15), (1, 2, 10, 16), (2, 2, 2, 6),
+                                                  (2, 2, 0, 7), (2, 2, 1, 8), (3, 2, 4, 4)])
+def test_period2_stop_around_launches(beta, alpha, seed, last):
+    img = _oscillating(40, 200, seed)
+    assert oracle.denoise_cycle(img, alpha, beta, 40)[1] == last + 1
+    for i, k in enumerate((last, last + 1, last + 2, last + 16, 40)):
+        _check(img, alpha, beta, k, cycle=True, in_place=i % 2 == 1, offset=i % 3)
+
+
+@pytest.mark.parametrize("beta", [1, 2, 3, 4])
+@pytest.mark.parametrize("rows,cols", [(1, 1), (2 * 4 + 1, COLS), (70, 2 * COLS - 1), (131, 3 * COLS + 16)])
+def test_period2_sizes(beta, rows, cols):
+    for i, k in enumerate((1, 2, 3, 6, 9, 24)):
+        img = synth.noisy_image(rows, cols, 0.3, 5 + i) if i % 2 == 0 else _oscillating(rows, cols, i)
+        _check(img, 8, beta, k, cycle=True, offset=i % 4, in_place=i % 3 == 1)
+
+
+# From 2^22 pixels on the first launch is shorter, and rows on dword boundaries
+# decide, with the pixels and passes, between deep and one-pass launches.
+@pytest.mark.parametrize("beta", [1, 2, 3, 4])
+@pytest.mark.parametrize("cols", [2048, 2051])
+def test_period2_large_images(beta, cols):
+    img = synth.noisy_image(2050, cols, 0.2, 9)
+    for k in (2, 3, 5, 9, 20):
+        got, ref = (_run(img, 20, beta, k, shape=s, cycle=True) for s in (DEEP, DENSE))
+        assert np.array_equal(got[0], ref[0]) and got[1:] == ref[1:], (beta, cols, k, got[1:], ref[1:])
+
+
+def test_period2_many_tiles_per_workgroup():
+    img = np.tile(synth.noisy_image(1100, 1200, 0.2, 9), (5, 5))[:5303, :5899]
+    got, ref = (_run(img, 20, 1, 40, shape=s, cycle=True) for s in (DEEP, DENSE))
+    assert np.array_equal(got[0], ref[0]) and got[1:] == ref[1:]
