@@ -15,16 +15,20 @@ on three streams), `single481` (481x321, 10%, alpha 20, beta 1, k 10).
 
 The JSON line also carries:
   roofline      the pass kernel as the step launches it (its average launch
-                duration from HIP events on its stream) against HBM: 2 B per
-                pixel and pass (read I, write I') over 8 TB/s -- for a shape
-                that skips unchanged tiles this is a dense-equivalent rate;
+                duration from HIP events on its stream; for the deep shape,
+                whose launches run several passes, the time per pass) against
+                HBM: 2 B per pixel and pass (read I, write I') over 8 TB/s --
+                for a shape that skips unchanged tiles or holds a tile for
+                several passes this is a dense-equivalent rate, which can
+                exceed 1;
                 traffic: measured HBM bytes per launch (rocprof counters)
   roofline_dense  the same for the dense one-pass kernel (every pixel of
                 every pass tested, every byte moved)
   kernels       the whole pass loop with each kernel shape: one launch per
                 pass with a host read-back per pass (the plain path), one
                 pass per launch dense, 2 and 4 passes per launch (temporal
-                blocking), change tracking, tile skipping
+                blocking), change tracking, tile skipping, and several
+                passes per launch that follow only what changed (deep)
   sync_call     one synchronous denoise call of the first run (results and
                 counts copied to the host), median wall time
   ceilings      the two ceilings measured on this GPU with the library's
@@ -51,7 +55,8 @@ if ROOT not in sys.path:
 
 METRIC = "Mpixel·iter/s & % HBM roofline, batched vs per-image launch; serve p50/p99 ms"
 HBM_PEAK_GBS = 8000.0
-KERNEL_SOURCE = os.path.join(ROOT, "paper_1306_5390_amd", "csrc", "pass_kernel.hpp")
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_1306_5390_amd", "csrc", n)
+                  for n in ("pass_kernel.hpp", "deep_kernel.hpp")]
 
 
 def parse():
@@ -101,8 +106,11 @@ def parse():
 
 def kernel_source_hash() -> str:
     import hashlib
-    with open(KERNEL_SOURCE, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+    h = hashlib.sha256()
+    for path in KERNEL_SOURCES:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
 def measured_traffic(workload, shape, avg_launch_s):
@@ -142,8 +150,12 @@ def _dispatches(csv_dir):
 
 
 def _pass_signature(name):
-    """(beta, T, rows, waves, TRACK) of a pass_kernel name, else None."""
+    """(beta, T, rows, waves, TRACK) of a pass_kernel name, (beta, "deep") of a
+    deep_kernel name, else None."""
     import re
+    m = re.search(r"deep_kernel<(\d+), (\d+), false>", name)
+    if m and "multi_deep" not in name:
+        return int(m.group(1)), "deep"
     m = re.search(r"pass_kernel<(\d+), (\d+), (\d+), (\d+), (\d+), (false|true)>", name)
     if not m or "multi_pass" in name:
         return None
@@ -183,6 +195,11 @@ def summarize_counters(workload, dirs, out_path=None):
     T3, R3, W3 = shapes[3]
     dense0 = (spec.beta, T3, R3, W3, 0)
     for s, (T, R, W) in enumerate(shapes):
+        if is_deep(phg, s):
+            # (with and without the dense lead launches)
+            deep = (spec.beta, "deep")
+            sig_of[frozenset({deep})] = sig_of[frozenset({deep, dense0})] = s
+            continue
         tr = 2 if phg.shape_skips_unchanged(s) else 1 if phg.shape_tracks_changes(s) else 0
         sig = {(spec.beta, T, R, W, tr)} if tr < 2 else {(spec.beta, 1, R, W, t) for t in (2, 3)}
         if tr > 0:
@@ -222,8 +239,10 @@ def summarize_counters(workload, dirs, out_path=None):
         per_launch_f = [sum(x) / len(x) for x in zip(*r["FETCH_SIZE"])]
         per_launch_w = [sum(x) / len(x) for x in zip(*r["WRITE_SIZE"])]
         per_launch = [a + b for a, b in zip(per_launch_f, per_launch_w)]
-        row = {"bytes_per_launch": sum(per_launch) / len(per_launch),
-               "algorithmic_bytes_per_launch": 2.0 * spec.rows * spec.cols * T_of[s],
+        # (a deep loop's launches run several passes each: its row is per pass)
+        deep = is_deep(phg, int(s))
+        row = {"bytes_per_launch": sum(per_launch) / (spec.k if deep else len(per_launch)),
+               "algorithmic_bytes_per_launch": 2.0 * spec.rows * spec.cols * (1 if deep else T_of[s]),
                "bytes_per_launch_in_order": [round(x) for x in per_launch],
                "launches": len(per_launch)}
         if s in sq:
@@ -299,8 +318,22 @@ def cpu_baseline(specs, images, band_rows=1024, band_cols=2048):
             "pinned_cpu": cpu, "nproc": nproc, "cpu_model": model}
 
 
+def is_deep(phg, s):
+    """The shape whose launches hold a tile for several passes."""
+    return tuple(phg.shapes()[s]) == (4, 8, 8)
+
+
+def counted_passes(phg, s):
+    """Passes a launch of shape `s` is counted with: launches of the deep
+    shape run up to 16 / beta, so its figures are per pass."""
+    return 1 if is_deep(phg, s) else phg.shapes()[s][0]
+
+
 def shape_name(phg, s):
     T, R, W = phg.shapes()[s]
+    if is_deep(phg, s):
+        return {"shape": s, "passes_per_launch": "up to 16 / beta", "rows_per_wave": R, "waves": W,
+                "kind": "deep"}
     kind = ("skipping" if phg.shape_skips_unchanged(s) else
             "tracked" if phg.shape_tracks_changes(s) else "dense")
     return {"shape": s, "passes_per_launch": T, "rows_per_wave": R, "waves": W, "kind": kind}
@@ -342,7 +375,7 @@ def time_denoise(phg, spec, d_in, dev, shape, reps):
             e1.record(s)
         torch.cuda.synchronize()
         ms = e0.elapsed_time(e1) / reps
-        T = phg.shapes()[shape][0]
+        T = counted_passes(phg, shape)
         launches = (spec.k + T - 1) // T
         assert int(it.item()) == iters
         return ms, iters, launches, out
@@ -500,13 +533,14 @@ def kernels_section(phg, spec, d_in, dev, reps, workload, ref_out):
             key = "tracked"
         elif n["kind"] == "skipping":
             key = "skipping_%dw" % W
+        elif n["kind"] == "deep":
+            key = "deep"
         if key and key not in pick:
             pick[key] = s
     rows = {}
     for key, s in pick.items():
         ms, iters, launches, out = time_denoise(phg, spec, d_in, dev, s, reps)
         assert torch.equal(out, ref_out), "shape %d differs from the headline output" % s
-        T = phg.shapes()[s][0]
         traffic, detail = measured_traffic(workload, s, ms * 1e-3 / launches)
         rows[key] = {**shape_name(phg, s), "ms_per_run": round(ms, 4), "iterations": iters,
                      "Mpx_iter_s": round(spec.rows * spec.cols * iters / (ms * 1e-3) / 1e6, 1),
@@ -734,7 +768,7 @@ def batch_section(n, steps, dev):
         "passes_run_of_planned": round(px_iters / px_passes_planned, 4),
         "roofline": {"bound": "hbm", "achieved": round(hbm, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(hbm / HBM_PEAK_GBS, 4),
-                     "kernel": "multi_pass_kernel (whole batch run, events)",
+                     "kernel": "batch pass launches (whole batch run, events)",
                      "note": "2 B per pixel and pass that ran, over the run's duration"},
         "batch_shapes": {str(bb): [phg.get_batch_tuning_class(bb, c) for c in range(3)]
                          for bb in (1, 2)},
@@ -952,14 +986,19 @@ def main():
     kernels, picked = None, {}
     ms_t, it_t, L_t, o_t = time_denoise(phg, s0, d0, dev, tuned_shape, args.kernel_reps)
     assert torch.equal(o_t, out0)
-    T_t = phg.shapes()[tuned_shape][0]
+    T_t = counted_passes(phg, tuned_shape)
     traffic, detail = measured_traffic(args.workload, tuned_shape, ms_t * 1e-3 / L_t)
     nm = shape_name(phg, tuned_shape)
     roofline = roofline_of(s0, ms_t, L_t, T_t, traffic, detail,
-                           kernel="pass_kernel<beta=%d, T=%d, rows=%d, waves=%d, %s>" % (
+                           kernel="deep_kernel<beta=%d, waves=%d>" % (s0.beta, nm["waves"])
+                           if nm["kind"] == "deep" else "pass_kernel<beta=%d, T=%d, rows=%d, waves=%d, %s>" % (
                                s0.beta, T_t, nm["rows_per_wave"], nm["waves"], nm["kind"]),
                            dense_equivalent=nm["kind"] != "dense")
-    if nm["kind"] != "dense":
+    if nm["kind"] == "deep":
+        roofline["launch_kernels"] = (
+            "launches of up to 16 / beta passes, on large images after dense one-pass launches "
+            "(1, 8, 4); avg_launch_us, launches and bytes are per pass")
+    elif nm["kind"] != "dense":
         roofline["launch_kernels"] = (
             "launches 0-1: the dense one-pass kernel (1, 8, 4); then the shape's own"
             + (" (launch 2 builds the tile lists, later launches run the listed tiles)"

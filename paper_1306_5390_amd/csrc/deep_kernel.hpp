@@ -34,13 +34,17 @@
 // that did not change in the previous launch or in this one are not stored
 // (the destination holds the output of the launch before the previous one).
 //
+// With the period-2 stop (CYC, see CyclePlan) every pass from a launch's second
+// on also tells exactly whether a pixel became other than two passes before.
+//
 // What bounds it: dense strips the VALU issue (1600 VALU instructions a strip
 // of 8 rows at beta 2, 1270 in pass_kernel.hpp); late passes the chain of LDS
 // latencies (about 1.1 us a pass); small images three launches' latency.
 // Measured against the one-pass launches it takes the place of (us per call):
-// 321 x 481, beta 1, k 10: 69 against 146; 2048^2, k 32: 108 against 268 at
-// beta 1, 122 against 361 at beta 2; 4099 x 4001, beta 1: 371 against 1041;
-// 8192^2, beta 2, half its pixels noise: 446 against 972.
+// 321 x 481, beta 1, k 10: 47 against 149; 2048^2, k 32: 106 against 270 at
+// beta 1, 109 against 367 at beta 2; 4099 x 4001, beta 1: 387 against 1052;
+// 8192^2, beta 2, half its pixels noise: 451 against 994; 1023 x 1537, beta 2,
+// with the period-2 stop: 90 against 335.
 #pragma once
 
 #include "pass_kernel.hpp"

@@ -593,7 +593,7 @@ static bool deep_cycle(const phgrms_params& p) {
 // The launch that comes to the stop runs its other passes too: nothing moves
 // any more, so a tile only counts them.  The image then alternates, so what
 // that launch stored is the result or the image before it, and in the latter
-// case one more pass makes the result.  1023 x 1537, beta 2, k 32: 81 us, 312
+// case one more pass makes the result.  1023 x 1537, beta 2, k 32: 90 us, 335
 // by one-pass launches.
 int enqueue_deep_cycle(const uint8_t* d_in, uint8_t* d_out, const phgrms_params& p, int shape, uint8_t* ws_img,
                        unsigned long long* counts, unsigned long long* changed, int* iterations, int* state,
