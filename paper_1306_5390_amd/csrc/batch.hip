@@ -2,10 +2,10 @@
 //
 // Each image of a batch runs the pass loop of Section 2 with its own size,
 // alpha, beta and k.  Instead of one launch sequence per image, the images
-// are spread over three streams (balanced by work) and, per stream, launch j
-// of every image with the same beta and kernel shape goes into one
-// multi_deep_kernel (or multi_pass_kernel) launch over a static table of all
-// their tiles.  The plan precomputes, per group, the tile tables and the
+// are spread over three streams (balanced by work; see share_launches) and,
+// per stream, launch j of every image with the same beta and kernel shape goes
+// into one multi_deep_kernel (or multi_pass_kernel) launch over a static table
+// of all their tiles.  The plan precomputes, per group, the tile tables and the
 // image descriptors of every launch index; a run uploads them once per set of pointers and replays the
 // whole sequence (forked to the streams and joined) as a HIP graph.
 #include <hip/hip_runtime.h>
@@ -155,6 +155,58 @@ struct TileTable {
   size_t off = 0;                   // in the workspace
 };
 
+// Workgroups that the device runs with a CU each.
+constexpr int kBatchCus = 256;
+
+// Owned rows of the deep tiles of a small batch: the fewest (but 4) with
+// which every CU has at most one tile of the whole batch, whose groups run
+// side by side; 0 where the tiles of full height are more.  A launch then
+// takes as long as one tile, so tiles are low and have 16 waves (8 images of 0.6
+// Mpixel, k 8: 127 us with high tiles, 116 with low ones, 103 with 16 waves as
+// well; for up to two or three tiles per CU it does not pay: 12 images of 2.6
+// Mpixel, k 16, 136 with high tiles, 149 and 141).
+int small_batch_rows(const phgrms_item* items, int n, const std::vector<int>& depth) {
+  if (std::count_if(depth.begin(), depth.end(), [](int d) { return d > 0; }) > kBatchCus) return 0;
+  for (int h = 4; h <= 64; ++h) {
+    long long tiles = 0;
+    for (int i = 0; i < n; ++i) {
+      if (depth[i] <= 0) continue;
+      const phgrms_params& p = items[i].p;
+      const TileGeom g = tile_geom(p, kDeepShape, depth[i]);
+      const int th = std::min(g.TH, h);
+      tiles += (long long)g.tiles_x * ((p.rows + th - 1) / th);
+    }
+    if (tiles <= kBatchCus) return h;
+  }
+  return 0;
+}
+
+constexpr long long kLargeBatch = 1ll << 24;   // pixels
+
+// Whether all images of one beta and shape share their launches, instead of
+// every stream having images of each.  A small batch is latency-bound: its
+// time is that of the longest chain of launches, and sharing leaves fewer in a
+// stream (us per run, every stream with images of each and shared: 8 images of
+// 0.6 Mpixel, k 8: 103 and 73; 12 of 2.6, k 16: 177 and 136; 40 of 8.8, k 32:
+// 326 and 240).  In a larger one the streams also overlap one launch's tail
+// with another's work: sharing pays as long as no beta has most of the work
+// (48 images of 20 Mpixel, k 32, half of them beta 1: 382 and 341, all of them
+// beta 1: 358 and 454; 60 of 75 Mpixel, k 16: 883 and 840) and up to 2^27
+// pixels (300 images of 400 Mpixel, k 32: 3690 to 4050 and 4070 to 4090).
+bool share_launches(const std::map<std::pair<int, int>, double>& kind_work, long long batch_px) {
+  // (the one-pass shapes' launches are long: every stream has some of each)
+  for (const auto& kw : kind_work)
+    if (!is_deep(kw.first.second)) return false;
+  if (batch_px < kLargeBatch) return true;
+  if (batch_px >= (1ll << 27)) return false;
+  double all = 0.0, most = 0.0;
+  for (const auto& kw : kind_work) {
+    all += kw.second;
+    most = std::max(most, kw.second);
+  }
+  return 3.0 * most <= 2.0 * all;
+}
+
 struct Group {
   int beta = 0;
   int shape = 0;
@@ -168,7 +220,19 @@ struct Group {
   // (a shape that is not deep has the first only)
   TileTable tables[3];
   size_t descs_off = 0;             // launches x images.size() ImageDesc
+  int rows[3] = {};                 // owned rows of a deep tile (small_batch_rows), or 0: all it can
   bool deep() const { return is_deep(shape); }
+  // small batch, launch j: 16 waves per tile
+  bool wide(int j) const { return rows[kind(j)] > 0 && beta < 4; }
+  TileGeom geom(const phgrms_params& p, int j) const {
+    TileGeom g = tile_geom(p, kernel_shape(j), depth(j));
+    if (rows[kind(j)] > 0 && rows[kind(j)] < g.TH) {
+      g.TH = rows[kind(j)];
+      g.tiles_y = (p.rows + g.TH - 1) / g.TH;
+      g.ntiles = (long long)g.tiles_x * g.tiles_y;
+    }
+    return g;
+  }
   int kind(int j) const { return !deep() || j < plan.lead ? 0 : j == plan.lead ? 1 : 2; }
   const TileTable& table(int j) const { return tables[kind(j)]; }
   int depth(int j) const { return j < plan.lead ? 1 : j == plan.lead ? plan.first : plan.rest; }
@@ -186,7 +250,7 @@ struct Group {
 LaunchPlan group_plan(int beta, int shape, long long batch_px) {
   if (!is_deep(shape)) return LaunchPlan{0, kShapes[shape].T, kShapes[shape].T};
   if (beta >= 3) return LaunchPlan{0, 4, 4};
-  if (batch_px < (1ll << 24)) return LaunchPlan{0, 8, 8};
+  if (batch_px < kLargeBatch) return LaunchPlan{0, 8, 8};
   return LaunchPlan{2, 6, beta == 1 ? 16 : 8};
 }
 
@@ -300,9 +364,11 @@ int enqueue_run(phgrms_plan* pl, uint8_t* ws, hipStream_t s) {
         return fail(PHGRMS_EDEVICE, "occupancy query of the listed batch kernel failed");
       // (change-tracking groups: the dense kernel for the first launches)
       const void* k = g.lists ? multi_skip_ptr(g.beta, g.shape, j)
+                        : g.wide(j) ? multi_deep_ptr(g.beta, true)
                               : multi_kernel_ptr(g.beta, shape, g.maps && j >= kDenseFirstLaunches);
       void* args[] = {&a};
-      e = hipLaunchKernel(k, dim3(grid), dim3(kShapes[shape].waves * 64), args, 0, gs);
+      const int waves = g.wide(j) ? kDeepWideWaves : kShapes[shape].waves;
+      e = hipLaunchKernel(k, dim3(grid), dim3(waves * 64), args, 0, gs);
       if (e != hipSuccess) return hip_fail(e, "batch pass launch");
     }
   }
@@ -396,23 +462,46 @@ int phgrms_batch_plan(const phgrms_item* items, int32_t n, const char* tune_cach
   // Images are spread over kSideStreams streams, largest work (tiles x
   // launches) first, each to the stream with the least work so far; a group
   // is the images of one stream that share (beta, kernel shape), one
-  // multi-image launch per launch index.
+  // multi-image launch per launch index.  Where sharing launches pays
+  // (share_launches), what is spread is all the images of one beta and shape.
   long long batch_px = 0;
   for (int i = 0; i < n; ++i) batch_px += (long long)items[i].p.rows * items[i].p.cols;
-  std::vector<int> order(n), stream_of(n, 0);
+  std::vector<int> stream_of(n, 0);
   std::vector<double> work(n, 0.0), load(kSideStreams, 0.0);
   for (int i = 0; i < n; ++i) {
-    order[i] = i;
     const int shp = batch_shape(items[i].p);
     const LaunchPlan lp = group_plan(items[i].p.beta, shp, batch_px);
     if ((int64_t)items[i].p.rows * items[i].p.cols > 0 && items[i].p.k > 0)
       work[i] = double(tile_geom(items[i].p, shp, lp.rest).ntiles) * double(lp.launch_of(items[i].p.k - 1) + 1);
   }
-  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return work[a] > work[b]; });
-  for (int i : order) {
+  std::map<std::pair<int, int>, double> kind_work;
+  for (int i = 0; i < n; ++i) kind_work[{items[i].p.beta, batch_shape(items[i].p)}] += work[i];
+  const bool share = share_launches(kind_work, batch_px);
+  std::map<std::pair<int, int>, std::vector<int>> units;
+  for (int i = 0; i < n; ++i)
+    units[share ? std::make_pair(items[i].p.beta, batch_shape(items[i].p)) : std::make_pair(-1, i)].push_back(i);
+  std::vector<std::pair<double, const std::vector<int>*>> by_work;
+  for (const auto& u : units) {
+    double w = 0.0;
+    for (int i : u.second) w += work[i];
+    by_work.emplace_back(w, &u.second);
+  }
+  std::stable_sort(by_work.begin(), by_work.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+  for (const auto& [w, images] : by_work) {
     const int k = int(std::min_element(load.begin(), load.end()) - load.begin());
-    stream_of[i] = k;
-    load[k] += work[i];
+    for (int i : *images) stream_of[i] = k;
+    load[k] += w;
+  }
+  // (per kind of launch, see Group::tables)
+  int rows[3] = {};
+  for (int kind = 1; kind < 3; ++kind) {
+    std::vector<int> depth(n, 0);
+    for (int i = 0; i < n; ++i) {
+      const int shp = batch_shape(items[i].p);
+      const LaunchPlan lp = group_plan(items[i].p.beta, shp, batch_px);
+      if (is_deep(shp) && work[i] > 0.0) depth[i] = kind == 1 ? lp.first : lp.rest;
+    }
+    rows[kind] = small_batch_rows(items, n, depth);
   }
   std::map<std::tuple<int, int, int>, int> gidx;
   for (int i = 0; i < n; ++i) {
@@ -427,6 +516,7 @@ int phgrms_batch_plan(const phgrms_item* items, int32_t n, const char* tune_cach
       g.plan = group_plan(b, shp, batch_px);
       g.maps = kShapes[g.shape].track != 0;
       g.lists = kShapes[g.shape].track == 2;
+      if (g.deep()) std::copy(rows, rows + 3, g.rows);
       pl->groups.push_back(g);
       pl->group_stream.push_back(stream_of[i]);
     }
@@ -441,7 +531,7 @@ int phgrms_batch_plan(const phgrms_item* items, int32_t n, const char* tune_cach
     for (int kind = 0; kind < 3; ++kind) {
       const int j = kind == 0 ? 0 : g.plan.lead + kind - 1;   // its first launch
       if (g.kind(j) != kind || j >= pl->launches[i]) continue;
-      const TileGeom tg = tile_geom(items[i].p, g.kernel_shape(j), g.depth(j));
+      const TileGeom tg = g.geom(items[i].p, j);
       for (long long t = 0; t < tg.ntiles; ++t) g.tables[kind].tiles.push_back(TileRef{local, int(t)});
     }
     if (g.deep()) {
@@ -588,7 +678,7 @@ int phgrms_batch_run(phgrms_plan* pl, const uint8_t* d_in, size_t in_bytes, uint
           x.pass0 = g.plan.start(j);
           x.npasses = passes(j);
           x.prev_passes = passes(j - 1);
-          const TileGeom tg = tile_geom(p, g.kernel_shape(j), g.depth(j));
+          const TileGeom tg = g.geom(p, j);
           x.tiles_x = tg.tiles_x;
           if (g.deep()) {
             // (the lead launches write no map; the first two launches of a

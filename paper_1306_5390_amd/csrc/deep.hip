@@ -28,14 +28,19 @@ const void* deep_cycle_ptr(int beta, bool wide) {
   return wide ? deep_ptr<kDeepWideWaves, true>(beta) : deep_ptr<kDeepWaves, true>(beta);
 }
 
-const void* multi_deep_ptr(int beta) {
+template <int WAVES>
+static const void* multi_ptr(int beta) {
   switch (beta) {
-    case 1: return reinterpret_cast<const void*>(&multi_deep_kernel<1, kDeepWaves>);
-    case 2: return reinterpret_cast<const void*>(&multi_deep_kernel<2, kDeepWaves>);
-    case 3: return reinterpret_cast<const void*>(&multi_deep_kernel<3, kDeepWaves>);
+    case 1: return reinterpret_cast<const void*>(&multi_deep_kernel<1, WAVES>);
+    case 2: return reinterpret_cast<const void*>(&multi_deep_kernel<2, WAVES>);
+    case 3: return reinterpret_cast<const void*>(&multi_deep_kernel<3, WAVES>);
     case 4: return reinterpret_cast<const void*>(&multi_deep_kernel<4, kDeepWaves>);
     default: return nullptr;
   }
+}
+
+const void* multi_deep_ptr(int beta, bool wide) {
+  return wide ? multi_ptr<kDeepWideWaves>(beta) : multi_ptr<kDeepWaves>(beta);
 }
 
 bool deep_fits(const phgrms_params& p) { return p.rows < (1 << 30) && p.cols < (1 << 30); }

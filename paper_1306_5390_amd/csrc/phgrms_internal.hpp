@@ -114,11 +114,12 @@ void apply_tuning(const TuneTables& t);
 const void* multi_kernel_ptr(int beta, int shape, bool maps = false);
 // Deep shapes (deep_kernel.hpp, deep.hip): kernels of one image and of many.
 inline bool is_deep(int shape) { return kShapes[shape].track == 3; }
+constexpr int kDeepShape = 13;
 constexpr int kDeepWaves = 8;      // waves of a workgroup
 constexpr int kDeepWideWaves = 16; // the same where no CU has more than one (beta 1 .. 3)
 const void* deep_kernel_ptr(int beta, bool wide);
 const void* deep_cycle_ptr(int beta, bool wide);   // the period-2 variant
-const void* multi_deep_ptr(int beta);
+const void* multi_deep_ptr(int beta, bool wide = false);
 // A tile's row and column arithmetic stays inside an int.
 bool deep_fits(const phgrms_params& p);
 // The launches of the pass loop.  `lead` dense launches of one pass come

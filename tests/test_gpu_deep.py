@@ -137,6 +137,49 @@ def test_batch_of_mixed_images(big, in_place):
     plan.close()
 
 
+# Up to 256 tiles a batch has low tiles of 16 waves (256 and 257 images of one
+# tile, 70 of four), and all images of one beta share their launches.
+@pytest.mark.parametrize("specs", [[(1, 1, 1, 3)], [(40, 200, b, 17) for b in (1, 2, 3, 4)],
+                                   [(300, 700, 1, 20), (301, 701, 2, 20), (131, 449, 3, 9), (500, 230, 4, 5)],
+                                   [(64, 4 * COLS, 1, 9)] * 70, [(30, COLS, 2, 9)] * 256, [(30, COLS, 2, 9)] * 257],
+                         ids=["one", "betas", "low", "four-tiles", "full", "over"])
+def test_small_batches(specs):
+    _check_batch([(r, c, 9, b, k) for r, c, b, k in specs],
+                 [_oscillating(r, c, i % 5) if i % 2 else synth.noisy_image(r, c, 0.3, i % 7)
+                  for i, (r, c, _, _) in enumerate(specs)])
+
+
+# From 2^24 pixels on images share launches only if no beta has most of the work.
+@pytest.mark.parametrize("betas", [(1, 2, 1, 2), (1, 1, 1, 2)])
+def test_large_batches(betas):
+    im = np.tile(synth.noisy_image(512, 600, 0.3, 5), (4, 4))[:, :2399]
+    specs = [im.shape + (20, b, 21) for b in betas]
+    want = {b: _run(im, 20, b, 21, shape=DENSE) for b in betas}
+    _check_batch(specs, [im] * len(betas), [want[b] for b in betas])
+
+
+def _check_batch(specs, imgs, want=None):
+    torch, m = _modules()
+    plan = m.Batch(specs)
+    src, dst = plan.new_arena(), plan.new_arena()
+    for i, im in enumerate(imgs):
+        plan.view(src, i).copy_(torch.from_numpy(im))
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    seen = {}
+    for _ in range(2):
+        plan.run(src, dst, stream=stream)
+        torch.cuda.synchronize()
+        for i, (s, im, (it, ch)) in enumerate(zip(specs, imgs, plan.results())):
+            key = (s, im.tobytes())
+            if key not in seen:
+                seen[key] = want[i] if want else oracle.denoise(im, s[2], s[3], s[4])
+            w = seen[key]
+            assert np.array_equal(plan.view(dst, i, out=True).cpu().numpy(), w[0]), (i, s)
+            assert it == w[1] and list(ch) == list(w[2])[:it], (i, s)
+    plan.close()
+
+
 @pytest.mark.parametrize("passes", [0, 1, 4, -1])
 def test_served_requests(passes):
     """Requests at different launches share a step's deep launch."""
