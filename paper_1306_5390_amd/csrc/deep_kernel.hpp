@@ -51,16 +51,9 @@
 
 namespace phg {
 
-constexpr int kDeepH = 64;                         // rows computed: WAVES strips of R rows, R <= 8 (R rows x
-                                                   // 8 words of bits, one lane each)
-constexpr int kDeepHalo = 16;                      // halo columns on each side: passes * BETA fit in it
-constexpr int kDeepCols = 256 - 2 * kDeepHalo;     // owned columns of a tile
 constexpr int kDeepMaxPasses = 16;
 constexpr int kDeepWords = 256;                    // most active words (of 4 pixels) of a strip tested one by one
 constexpr int kDeepListMost = 64;                  // most changed pixels of a tile followed by list
-
-// Most passes of one launch at `beta`.
-__host__ __device__ constexpr int deep_max_passes(int beta) { return kDeepHalo / beta; }
 
 struct DeepTile {
   const uint8_t* src;
@@ -79,10 +72,6 @@ struct DeepTile {
   uint8_t* cnt_out;          // launch's last pass changed
   int full_store;            // 1: the destination does not hold the image of two launches back
 };
-
-__host__ __device__ inline int deep_tiles_x(int cols) {
-  return int((static_cast<long long>(cols) + kDeepCols - 1) / kDeepCols);
-}
 
 // ---- pieces of both kernels --------------------------------------------------------
 

@@ -387,6 +387,10 @@ size_t change_map_bytes(int rows, int cols) {
   return list_state_offset(rows, cols) + 4 * TileLists::words(list_capacity(rows, cols));
 }
 
+static bool deep_maps_fit(const phgrms_params& p) {
+  return 2 * (sizeof(uint32_t) + 1) * deep_map_words(p.rows, p.cols) <= change_map_bytes(p.rows, p.cols);
+}
+
 static bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
   const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
   return na > 0 && nb > 0 && x < y + nb && y < x + na;
@@ -437,7 +441,12 @@ int enqueue_denoise(const uint8_t* d_in, uint8_t* d_out, const phgrms_params& p,
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "init launch");
   }
   const bool deep = is_deep(shape);
-  const LaunchPlan plan = deep ? deep_plan(p) : LaunchPlan{0, kShapes[shape].T, kShapes[shape].T};
+  // deep shapes: two change maps, one word and one count byte per row and tile column, in the
+  // space of the other shapes' maps and lists where they fit (without them
+  // every launch tests every pixel in its first pass)
+  const size_t deep_map = deep_map_words(p.rows, p.cols);
+  const bool deep_maps = deep && maps != nullptr && deep_maps_fit(p);
+  const LaunchPlan plan = deep ? deep_plan(p, deep_maps) : LaunchPlan{0, kShapes[shape].T, kShapes[shape].T};
   const int L = p.k > 0 ? plan.launch_of(p.k - 1) + 1 : 0;
   const TileGeom g = tile_geom(p, shape);
   auto dst_of = [&](int j) -> uint8_t* { return ((L - 1 - j) % 2 == 0) ? d_out : ws_img; };
@@ -451,12 +460,6 @@ int enqueue_denoise(const uint8_t* d_in, uint8_t* d_out, const phgrms_params& p,
     src = ws_img;
     src0 = ws_img;
   }
-  // deep shapes: two change maps, one word and one count byte per row and tile column, in the
-  // space of the other shapes' maps and lists where they fit (without them
-  // every launch tests every pixel in its first pass)
-  const size_t deep_map = deep_map_words(p.rows, p.cols);
-  const bool deep_maps = deep && maps != nullptr &&
-                         2 * (sizeof(uint32_t) + 1) * deep_map <= change_map_bytes(p.rows, p.cols);
   if (n > 0) {
     for (int j = 0; j < L; ++j) {
       if (deep && j >= plan.lead) {
@@ -503,8 +506,9 @@ int enqueue_denoise(const uint8_t* d_in, uint8_t* d_out, const phgrms_params& p,
       const size_t half = map_half_bytes(p.rows, p.cols);
       const bool track = maps != nullptr && !deep && g.T == 1 && kShapes[shape].track;
       const bool dense0 = deep || (track && j < kDenseFirstLaunches);
+      const int dense_shape = deep ? one_pass_shape(p.beta, n, false) : kDefaultShape;
       if (dense0) {
-        const TileGeom gd = tile_geom(p, kDefaultShape);
+        const TileGeom gd = tile_geom(p, dense_shape);
         a.tiles_x = gd.tiles_x;
         a.ntiles = int(gd.ntiles);
       }
@@ -521,7 +525,7 @@ int enqueue_denoise(const uint8_t* d_in, uint8_t* d_out, const phgrms_params& p,
       a.prev2 = (diff2 == nullptr || j == 0) ? nullptr : (j == 1 ? src0 : a.dst);
       // (skipping shapes: from launch 2 on, the destination holds the
       // output of launch j-2, which is kept where nothing can change)
-      if ((e = launch_pass(p.beta, dense0 ? kDefaultShape : shape, a, s)) != hipSuccess)
+      if ((e = launch_pass(p.beta, dense0 ? dense_shape : shape, a, s)) != hipSuccess)
         return hip_fail(e, "pass launch");
       src = a.dst;
     }
@@ -547,47 +551,9 @@ int enqueue_denoise(const uint8_t* d_in, uint8_t* d_out, const phgrms_params& p,
   return PHGRMS_OK;
 }
 
-// Launches after the first run an odd number of passes: their stored image is
-// an even number of passes on, so that tiles that alternate are idle.  Large
-// images have the shorter first launch: its passes test every pixel of the
-// halo too (k 20, us per call, with the longer first launch and with the
-// shorter: 8192^2: 1062 and 877 at beta 1, 719 and 648 at beta 2, 431 and 386
-// at beta 3; 2048^2: 131 and 116, 92 and 79, 64 and 64; but 1023 x 1537, k 8,
-// beta 2: 44 and 52).
-static CyclePlan cycle_plan(const phgrms_params& p) {
-  const bool large = (int64_t)p.rows * p.cols >= (int64_t(1) << 22);
-  return p.beta == 1   ? CyclePlan{p.k, large ? 8 : 16, 15}
-         : p.beta == 2 ? CyclePlan{p.k, large ? 6 : 8, 7}
-         : p.beta == 3 ? CyclePlan{p.k, large ? 3 : 4, 5} : CyclePlan{p.k, 4, 3};
-}
-
 // Whether the period-2 stop runs by deep launches: where their change maps
-// fit, and the one-pass launches are not as fast.  Those are, with their
-// smaller halo and a finish of one launch, for the first few passes of a large
-// image whose rows start on dword boundaries, and more so at the larger betas
-// (us per call, one-pass and deep, a tenth of the pixels noise or, at beta 1,
-// four tenths; 512^2, beta 1, k 2: 21 and 23; 4096^2: beta 1, k 4: 103 and
-// 120, k 6: 145 and 147, a tenth noise 118 and 81; beta 2, k 3: 106 and 110,
-// k 4: 144 and 120; beta 3, k 6: 239 and 278, k 10: 392 and 349; 2048^2, beta
-// 4, k 6: 122 and 148, k 10: 199 and 183; 8192^2, beta 1, k 10: 667 and 691,
-// k 12: 786 and 739).  At beta 4 large images are faster by the one or by the
-// other, as their noise is (4096^2, k 32: 905 and 674, four tenths noise 193
-// and 296), and stay with the one-pass launches.
-static bool deep_cycle(const phgrms_params& p) {
-  const int64_t n = (int64_t)p.rows * p.cols;
-  if (p.k <= 1 || n <= 0 || !deep_fits(p) ||
-      2 * (sizeof(uint32_t) + 1) * deep_map_words(p.rows, p.cols) > change_map_bytes(p.rows, p.cols))
-    return false;
-  const bool huge = n >= (int64_t(1) << 25);
-  if ((p.cols & 3) != 0) return p.beta < 4 || !huge;
-  if (n < (int64_t(1) << 21)) return p.k > 2 || n < (int64_t(1) << 18);
-  switch (p.beta) {
-    case 1: return p.k > (huge ? 10 : 4);
-    case 2: return p.k > 3;
-    case 3: return p.k > 8;
-    default: return p.k > 8 && n < (int64_t(1) << 23);
-  }
-}
+// fit, and the one-pass launches are not as fast.
+static bool deep_cycle(const phgrms_params& p) { return cycle_plan_pays(p) && deep_maps_fit(p); }
 
 // As enqueue_denoise, with the period-2 stop, by deep launches (CyclePlan).
 // The launch that comes to the stop runs its other passes too: nothing moves

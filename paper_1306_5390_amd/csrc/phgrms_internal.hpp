@@ -8,6 +8,7 @@
 
 #include "phgrms.h"
 #include "host_common.hpp"
+#include "plan.hpp"
 
 namespace phg {
 
@@ -16,23 +17,6 @@ constexpr int kDefaultShape = 3;   // (1, 8, 4): one pass, 8 rows per wave, 4 wa
 // kernel of kDefaultShape (no change maps).  At most 2: the list-building
 // launch of a skipping shape is launch 2.
 constexpr int kDenseFirstLaunches = 2;
-// The launches of a deep loop with the period-2 stop: a pass can be compared
-// with the image two passes before only if the launch has that one, so every
-// launch but the first begins with the last pass of the launch before, which
-// stores the image as it was before that pass (the last launch: after it).
-// `first` passes in launch 0, `rest` in the others.
-struct CyclePlan {
-  int k, first, rest;
-  __host__ __device__ int start(int j) const { return j == 0 ? 0 : first - 1 + (j - 1) * (rest - 1); }
-  __host__ __device__ int passes(int j) const {
-    const int n = j == 0 ? first : rest, left = k - start(j);
-    return n < left ? n : left;
-  }
-  __host__ __device__ bool last(int j) const { return start(j) + passes(j) >= k; }
-  // passes after which launch j's stored image is taken
-  __host__ __device__ int advance(int j) const { return last(j) ? passes(j) : passes(j) - 1; }
-};
-
 // Workgroups of a launch over listed tiles, in multiples of the grid that
 // fits on the device at once.
 constexpr int kListedOversubscription = 4;
@@ -57,21 +41,6 @@ struct TileGeom {
 // the rows that spread one image over the device (alone: the image has the
 // launch to itself) or of the most rows they can own.
 TileGeom tile_geom(const phgrms_params& p, int shape, int depth = 0, bool alone = false);
-
-// How a pass loop of k passes is cut into launches: `lead` launches of one
-// pass, one launch of `first`, then launches of `rest` each.
-struct LaunchPlan {
-  int lead, first, rest;
-  __host__ __device__ int start(int j) const {   // first pass of launch j
-    return j <= lead ? j : lead + first + (j - lead - 1) * rest;
-  }
-  // (no launch has 256 passes; a shape that is not deep has lead 0)
-  __host__ __device__ int packed() const { return lead | first << 8 | rest << 16; }
-  __host__ __device__ static LaunchPlan unpacked(int v) { return LaunchPlan{v & 255, (v >> 8) & 255, (v >> 16) & 255}; }
-  __host__ __device__ int launch_of(int pass) const {
-    return pass < lead ? pass : pass < lead + first ? lead : lead + 1 + (pass - lead - first) / rest;
-  }
-};
 
 struct WsLayout {
   size_t state_off;    // int32 iteration count
@@ -120,24 +89,6 @@ constexpr int kDeepWideWaves = 16; // the same where no CU has more than one (be
 const void* deep_kernel_ptr(int beta, bool wide);
 const void* deep_cycle_ptr(int beta, bool wide);   // the period-2 variant
 const void* multi_deep_ptr(int beta, bool wide = false);
-// A tile's row and column arithmetic stays inside an int.
-bool deep_fits(const phgrms_params& p);
-// The launches of the pass loop.  `lead` dense launches of one pass come
-// first where every pixel has to be tested and the image is large: the dense
-// kernel tests it with no halo (2048^2, beta 2, k 32: 105 us with two,
-// 115 with none; 8192^2 433 and 463), while on smaller images the launches
-// cost more than the halo (1024^2: 80 and 73).  At beta 1 the dense pass is
-// cheaper, so that this pays from 2^25 pixels (8192^2: 1176 and 1234; 4099 x
-// 4001: 396 and 378).  The last launches have an even number of passes, so
-// that tiles that only alternate need not run.
-LaunchPlan deep_plan(const phgrms_params& p);
-// Owned rows of a tile of an image alone on the device: the fewest (but 4)
-// that give every CU at most one tile, else the most that a tile can own.
-// (997 x 1031, beta 3: 46 us with 250 tiles, 51 with 125 or with 315.)
-int deep_rows(int rows, int cols, int beta, int depth, int cus);
-// Words of a change map (a map has a word and a count byte per image row and
-// tile column).
-size_t deep_map_words(int rows, int cols);
 int device_cus();                  // of the current device, or -1
 // The one-pass shape that stands in for a deep one.
 int one_pass_shape(int beta, long long npx, bool tracking);

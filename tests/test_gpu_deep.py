@@ -238,3 +238,21 @@ def test_period2_many_tiles_per_workgroup():
     img = np.tile(synth.noisy_image(1100, 1200, 0.2, 9), (5, 5))[:5303, :5899]
     got, ref = (_run(img, 20, 1, 40, shape=s, cycle=True) for s in (DEEP, DENSE))
     assert np.array_equal(got[0], ref[0]) and got[1:] == ref[1:]
+
+
+# The longest loops that run by one-pass launches only, one and three passes more, in
+# each range of sizes that the rule tells apart (the largest against the dense shape).
+@pytest.mark.parametrize("beta,rows,cols,few", [(1, 96, 128, 1), (2, 97, 129, 1), (3, 1024, 1024, 1), (4, 500, 512, 2),
+                                                (4, 1024, 1024, 4), (1, 2048, 1024, 3), (2, 2048, 1024, 3),
+                                                (3, 2048, 1024, 3), (4, 2048, 1024, 5), (3, 2048, 2304, 3),
+                                                (4, 2048, 2304, 4), (4, 2049, 2305, 2), (1, 4096, 4096, 4),
+                                                (3, 4096, 4096, 3), (4, 8192, 256, 10), (1, 8192, 256, 6)])
+def test_short_loops(beta, rows, cols, few):
+    for i, k in enumerate((few, few + 1, few + 3)):
+        img = synth.noisy_image(rows, cols, 0.2, i) if rows * cols < 1 << 20 else \
+            np.tile(synth.noisy_image(256, 256, 0.2, i), (rows // 256 + 1, cols // 256 + 1))[:rows, :cols].copy()
+        if rows * cols < 1 << 20:
+            _check(img, 20, beta, k, offset=i, in_place=i % 2 == 1)
+        else:
+            got, ref = _run(img, 20, beta, k, in_place=i % 2 == 1), _run(img, 20, beta, k, shape=DENSE)
+            assert np.array_equal(got[0], ref[0]) and got[1:] == ref[1:]

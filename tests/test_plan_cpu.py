@@ -1,0 +1,76 @@
+"""The rules by which a pass loop is cut into launches (plan.cpp), on the CPU:
+every pass once, no launch of more passes than a tile's halo holds, and the
+short loops, which one-pass launches run faster, without deep ones."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1306_5390_amd", "csrc")
+HALO = 16                        # columns, and rows at most, around a tile
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not installed")
+
+
+@pytest.fixture(scope="module")
+def plans(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("plan") / "plan_driver")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-fsanitize=undefined", "-fno-sanitize-recover=all",
+                    "-I", CSRC, "-I", os.path.join(ROOT, "include"), "-o", exe,
+                    os.path.join(ROOT, "tests", "sanitize", "plan_driver.cpp"), os.path.join(CSRC, "plan.cpp")],
+                   check=True)
+
+    def run(cases):
+        """Per case (rows, cols, beta, k, maps): few, lead, launches, cycle launches, cycle pays."""
+        text = "".join("%d %d %d %d %d\n" % c for c in cases)
+        out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout
+        got = []
+        for line in out.splitlines():
+            left, right = line.split("|")
+            few, lead, *launches = left.split()
+            *cycle, pays = right.split()
+            got.append((int(few), int(lead), [tuple(map(int, x.split(":"))) for x in launches],
+                        [tuple(map(int, x.split(":"))) for x in cycle], pays == "1"))
+        assert len(got) == len(cases)
+        return got
+    return run
+
+
+SIZES = [(1, 1), (9, 224), (128, 128), (321, 481), (1024, 1024), (997, 1031), (1448, 1449), (2048, 1024),
+         (2048, 2048), (2403, 3201), (4096, 4096), (4099, 4001), (6001, 8001), (8192, 8192), (46340, 46340),
+         (8192, 256), (1 << 30, 1), (1, (1 << 31) - 1)]
+
+
+def test_every_pass_once_within_the_halo(plans):
+    cases = [(r, c, b, k, m) for r, c in SIZES for b in (1, 2, 3, 4) for k in (*range(41), 1023, 1024) for m in (0, 1)]
+    for (_, _, beta, k, _), (_, lead, launches, cycle, _) in zip(cases, plans(cases)):
+        at = 0
+        for j, (start, passes) in enumerate(launches):
+            assert start == at and 1 <= passes <= HALO // beta and (j >= lead or passes == 1)
+            at += passes
+        assert at == k
+        # each launch but the first begins with the last pass of the one before
+        for j, (start, passes, advance) in enumerate(cycle):
+            assert 2 <= passes <= HALO // beta and (j == 0 or start == at)
+            at = start + passes - 1
+            assert advance == (passes if j + 1 == len(cycle) else passes - 1)
+            # so that tiles that only alternate are where they were
+            assert j == 0 or j + 1 == len(cycle) or advance % 2 == 0
+        assert k <= 1 or at == k - 1
+
+
+# (rows, cols, beta): the longest loop without a deep launch
+@pytest.mark.parametrize("rows,cols,beta,few", [
+    (128, 128, 1, 1), (1024, 1024, 2, 1), (2048, 2048, 1, 3), (4096, 4096, 1, 4), (8192, 8192, 1, 4),
+    (2048, 2048, 2, 3), (8192, 8192, 2, 3), (2048, 2048, 3, 3), (8192, 8192, 3, 3), (512, 512, 4, 2),
+    (1024, 1024, 4, 4), (2048, 2048, 4, 5), (8192, 8192, 4, 4), (997, 1031, 3, 1), (4099, 4001, 4, 2)])
+def test_short_loops_run_by_one_pass_launches(plans, rows, cols, beta, few):
+    for k, (_, lead, launches, _, _) in zip(range(1, 12), plans([(rows, cols, beta, k, 1) for k in range(1, 12)])):
+        assert (lead == k and len(launches) == k) == (k <= few), (k, launches)
+
+
+def test_images_without_interior_pixels(plans):
+    for (_, lead, _, _, _) in plans([(9, 8, 4, 32, 1), (8, 900, 4, 32, 1), (2, 70000, 1, 32, 1)]):
+        assert lead == 32
