@@ -181,8 +181,6 @@ int small_batch_rows(const phgrms_item* items, int n, const std::vector<int>& de
   return 0;
 }
 
-constexpr long long kLargeBatch = 1ll << 24;   // pixels
-
 // Whether all images of one beta and shape share their launches, instead of
 // every stream having images of each.  A small batch is latency-bound: its
 // time is that of the longest chain of launches, and sharing leaves fewer in a
@@ -239,19 +237,9 @@ struct Group {
   int kernel_shape(int j) const { return deep() && j < plan.lead ? kDefaultShape : shape; }
 };
 
-// How a group's loops are cut into launches.  Deep: in a large batch two
-// dense one-pass launches come first, since its images fill the device and
-// the halo of a deep tile is all cost while every pixel is tested, and at
-// beta 1 the later launches take 16 passes (150 images of 192 Mpixel, k 32:
-// 2.39 ms; without the dense launches 2.99, with 8 passes 2.48).  A small
-// batch is latency-bound, and takes fewer launches of smaller halo (12 images
-// of 1.5 Mpixel, k 16: 176 us against 204; 48 images of 20 Mpixel: 413
-// against 379).
-LaunchPlan group_plan(int beta, int shape, long long batch_px) {
-  if (!is_deep(shape)) return LaunchPlan{0, kShapes[shape].T, kShapes[shape].T};
-  if (beta >= 3) return LaunchPlan{0, 4, 4};
-  if (batch_px < kLargeBatch) return LaunchPlan{0, 8, 8};
-  return LaunchPlan{2, 6, beta == 1 ? 16 : 8};
+// How an image's loop is cut into launches (the same for all images of a group).
+LaunchPlan group_plan(const phgrms_params& p, int shape, long long batch_px) {
+  return is_deep(shape) ? deep_batch_plan(p.beta, p.k, batch_px) : LaunchPlan{0, kShapes[shape].T, kShapes[shape].T};
 }
 
 }  // namespace
@@ -461,25 +449,28 @@ int phgrms_batch_plan(const phgrms_item* items, int32_t n, const char* tune_cach
   }
   // Images are spread over kSideStreams streams, largest work (tiles x
   // launches) first, each to the stream with the least work so far; a group
-  // is the images of one stream that share (beta, kernel shape), one
-  // multi-image launch per launch index.  Where sharing launches pays
-  // (share_launches), what is spread is all the images of one beta and shape.
+  // is the images of one stream that share (beta, kernel shape, launch plan),
+  // one multi-image launch per launch index.  Where sharing launches pays
+  // (share_launches), what is spread is all the images that share these.
   long long batch_px = 0;
   for (int i = 0; i < n; ++i) batch_px += (long long)items[i].p.rows * items[i].p.cols;
   std::vector<int> stream_of(n, 0);
   std::vector<double> work(n, 0.0), load(kSideStreams, 0.0);
   for (int i = 0; i < n; ++i) {
     const int shp = batch_shape(items[i].p);
-    const LaunchPlan lp = group_plan(items[i].p.beta, shp, batch_px);
+    const LaunchPlan lp = group_plan(items[i].p, shp, batch_px);
     if ((int64_t)items[i].p.rows * items[i].p.cols > 0 && items[i].p.k > 0)
       work[i] = double(tile_geom(items[i].p, shp, lp.rest).ntiles) * double(lp.launch_of(items[i].p.k - 1) + 1);
   }
   std::map<std::pair<int, int>, double> kind_work;
   for (int i = 0; i < n; ++i) kind_work[{items[i].p.beta, batch_shape(items[i].p)}] += work[i];
   const bool share = share_launches(kind_work, batch_px);
-  std::map<std::pair<int, int>, std::vector<int>> units;
-  for (int i = 0; i < n; ++i)
-    units[share ? std::make_pair(items[i].p.beta, batch_shape(items[i].p)) : std::make_pair(-1, i)].push_back(i);
+  std::map<std::tuple<int, int, int>, std::vector<int>> units;
+  for (int i = 0; i < n; ++i) {
+    const int shp = batch_shape(items[i].p);
+    units[share ? std::make_tuple(items[i].p.beta, shp, group_plan(items[i].p, shp, batch_px).packed())
+                : std::make_tuple(-1, -1, i)].push_back(i);
+  }
   std::vector<std::pair<double, const std::vector<int>*>> by_work;
   for (const auto& u : units) {
     double w = 0.0;
@@ -498,22 +489,23 @@ int phgrms_batch_plan(const phgrms_item* items, int32_t n, const char* tune_cach
     std::vector<int> depth(n, 0);
     for (int i = 0; i < n; ++i) {
       const int shp = batch_shape(items[i].p);
-      const LaunchPlan lp = group_plan(items[i].p.beta, shp, batch_px);
-      if (is_deep(shp) && work[i] > 0.0) depth[i] = kind == 1 ? lp.first : lp.rest;
+      const LaunchPlan lp = group_plan(items[i].p, shp, batch_px);
+      if (is_deep(shp) && work[i] > 0.0 && lp.lead < items[i].p.k) depth[i] = kind == 1 ? lp.first : lp.rest;
     }
     rows[kind] = small_batch_rows(items, n, depth);
   }
-  std::map<std::tuple<int, int, int>, int> gidx;
+  std::map<std::tuple<int, int, int, int>, int> gidx;
   for (int i = 0; i < n; ++i) {
     const int b = items[i].p.beta;
     const int shp = batch_shape(items[i].p);
-    const auto key = std::make_tuple(stream_of[i], b, shp);
+    const LaunchPlan lp = group_plan(items[i].p, shp, batch_px);
+    const auto key = std::make_tuple(stream_of[i], b, shp, lp.packed());
     if (!gidx.count(key)) {
       gidx[key] = int(pl->groups.size());
       Group g;
       g.beta = b;
       g.shape = shp;
-      g.plan = group_plan(b, shp, batch_px);
+      g.plan = lp;
       g.maps = kShapes[g.shape].track != 0;
       g.lists = kShapes[g.shape].track == 2;
       if (g.deep()) std::copy(rows, rows + 3, g.rows);

@@ -82,6 +82,31 @@ LaunchPlan deep_plan(const phgrms_params& p, bool maps) {
   return pl;
 }
 
+// In a large batch two
+// dense one-pass launches come first, since its images fill the device and
+// the halo of a deep tile is all cost while every pixel is tested, and at
+// beta 1 the later launches take 16 passes (150 images of 192 Mpixel, k 32:
+// 2.39 ms; without the dense launches 2.99, with 8 passes 2.48).  A small
+// batch is latency-bound, and takes fewer launches of smaller halo (12 images
+// of 1.5 Mpixel, k 16: 176 us against 204; 48 images of 20 Mpixel: 413
+// against 379).
+// Images of up to three passes have dense launches only, from 2^22 pixels on
+// (us per run, a tenth noise, with deep launches, with dense ones, and before
+// there were deep ones: 8 images of 8 Mpixel, beta 3, k 2: 86, 68, 72; 12 of 50
+// Mpixel, beta 4, k 3: 746, 549, 557; 4 of 17 Mpixel, beta 2, k 3: 130, 102,
+// 115); at beta 4 the shortest already from 2^21 (12 of 3 Mpixel, k 2: 71, 60,
+// 64).  Those of four (beta 4) and of four and five (beta 3) have one dense
+// launch first (12 of 50 Mpixel, beta 3, k 5: 652, 541, 561); longer ones lose
+// by it on much noise what they gain on little (k 16: 776 and 721, two fifths
+// noise 403 and 418).
+LaunchPlan deep_batch_plan(int beta, int k, int64_t batch_px) {
+  const bool most = batch_px >= (1 << 22);
+  if ((k <= 3 && most) || (beta == 4 && k <= 2 && batch_px >= (1 << 21))) return LaunchPlan{3, 1, 1};
+  if (beta >= 3) return LaunchPlan{most && k <= (beta == 3 ? 5 : 4) ? 1 : 0, 4, 4};
+  if (batch_px < kLargeBatch) return LaunchPlan{0, 8, 8};
+  return LaunchPlan{2, 6, beta == 1 ? 16 : 8};
+}
+
 int deep_rows(int rows, int cols, int beta, int depth, int cus) {
   const int most = kDeepH - 2 * (depth - 1) * beta;
   const int tiles_x = deep_tiles_x(cols);

@@ -60,6 +60,9 @@ LaunchPlan deep_plan(const phgrms_params& p, bool maps);
 // The longest loop (in passes) of an image that runs by one-pass launches
 // only.
 int deep_few_passes(const phgrms_params& p, bool maps);
+// The launches of an image's loop in a batch of batch_px pixels.
+LaunchPlan deep_batch_plan(int beta, int k, int64_t batch_px);
+constexpr int64_t kLargeBatch = 1 << 24;   // pixels
 // The launches of a loop with the period-2 stop, and whether it runs by them
 // where the change maps fit (else by one-pass launches).
 CyclePlan cycle_plan(const phgrms_params& p);

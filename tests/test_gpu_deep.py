@@ -256,3 +256,14 @@ def test_short_loops(beta, rows, cols, few):
         else:
             got, ref = _run(img, 20, beta, k, in_place=i % 2 == 1), _run(img, 20, beta, k, shape=DENSE)
             assert np.array_equal(got[0], ref[0]) and got[1:] == ref[1:]
+
+
+# Loops of a batch that have dense launches only, or one ahead of the deep ones, beside longer ones.
+def test_batch_of_short_loops():
+    specs, imgs = [], []
+    for beta in (1, 2, 3, 4):
+        for k in range(1, 8):
+            imgs.append(synth.noisy_image(600 + k, 620 + beta, 0.3, 10 * beta + k))
+            specs.append(imgs[-1].shape + (20, beta, k))
+    assert sum(im.size for im in imgs) > 1 << 23
+    _check_batch(specs, imgs, [_run(im, *s[2:], shape=DENSE) for s, im in zip(specs, imgs)])

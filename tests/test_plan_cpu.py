@@ -23,16 +23,18 @@ def plans(tmp_path_factory):
                    check=True)
 
     def run(cases):
-        """Per case (rows, cols, beta, k, maps): few, lead, launches, cycle launches, cycle pays."""
-        text = "".join("%d %d %d %d %d\n" % c for c in cases)
+        """Per case (rows, cols, beta, k, maps[, pixels of the batch]): few, lead, launches,
+        cycle launches, cycle pays, the same two of a batch's image."""
+        text = "".join("%d %d %d %d %d %d\n" % (*c, *(() if len(c) == 6 else (c[0] * c[1],))) for c in cases)
         out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout
         got = []
         for line in out.splitlines():
-            left, right = line.split("|")
+            left, right, batch, _ = line.split("|")
             few, lead, *launches = left.split()
             *cycle, pays = right.split()
             got.append((int(few), int(lead), [tuple(map(int, x.split(":"))) for x in launches],
-                        [tuple(map(int, x.split(":"))) for x in cycle], pays == "1"))
+                        [tuple(map(int, x.split(":"))) for x in cycle], pays == "1",
+                        int(batch.split()[0]), [tuple(map(int, x.split(":"))) for x in batch.split()[1:]]))
         assert len(got) == len(cases)
         return got
     return run
@@ -45,12 +47,13 @@ SIZES = [(1, 1), (9, 224), (128, 128), (321, 481), (1024, 1024), (997, 1031), (1
 
 def test_every_pass_once_within_the_halo(plans):
     cases = [(r, c, b, k, m) for r, c in SIZES for b in (1, 2, 3, 4) for k in (*range(41), 1023, 1024) for m in (0, 1)]
-    for (_, _, beta, k, _), (_, lead, launches, cycle, _) in zip(cases, plans(cases)):
-        at = 0
-        for j, (start, passes) in enumerate(launches):
-            assert start == at and 1 <= passes <= HALO // beta and (j >= lead or passes == 1)
-            at += passes
-        assert at == k
+    for (_, _, beta, k, _), (_, lead, launches, cycle, _, blead, batch) in zip(cases, plans(cases)):
+        for ahead, plan in ((lead, launches), (blead, batch)):
+            at = 0
+            for j, (start, passes) in enumerate(plan):
+                assert start == at and 1 <= passes <= HALO // beta and (j >= ahead or passes == 1)
+                at += passes
+            assert at == k
         # each launch but the first begins with the last pass of the one before
         for j, (start, passes, advance) in enumerate(cycle):
             assert 2 <= passes <= HALO // beta and (j == 0 or start == at)
@@ -67,10 +70,21 @@ def test_every_pass_once_within_the_halo(plans):
     (2048, 2048, 2, 3), (8192, 8192, 2, 3), (2048, 2048, 3, 3), (8192, 8192, 3, 3), (512, 512, 4, 2),
     (1024, 1024, 4, 4), (2048, 2048, 4, 5), (8192, 8192, 4, 4), (997, 1031, 3, 1), (4099, 4001, 4, 2)])
 def test_short_loops_run_by_one_pass_launches(plans, rows, cols, beta, few):
-    for k, (_, lead, launches, _, _) in zip(range(1, 12), plans([(rows, cols, beta, k, 1) for k in range(1, 12)])):
+    for k, (_, lead, launches, *_) in zip(range(1, 12), plans([(rows, cols, beta, k, 1) for k in range(1, 12)])):
         assert (lead == k and len(launches) == k) == (k <= few), (k, launches)
 
 
 def test_images_without_interior_pixels(plans):
-    for (_, lead, _, _, _) in plans([(9, 8, 4, 32, 1), (8, 900, 4, 32, 1), (2, 70000, 1, 32, 1)]):
+    for (_, lead, *_) in plans([(9, 8, 4, 32, 1), (8, 900, 4, 32, 1), (2, 70000, 1, 32, 1)]):
         assert lead == 32
+
+
+# (pixels of the batch, beta): the longest loop without a deep launch, and the longest with
+# one dense launch ahead (beta 3 and 4)
+@pytest.mark.parametrize("px,beta,few,one", [(1 << 20, 1, 0, 0), (1 << 20, 4, 0, 0), (3 << 20, 4, 2, 0),
+                                             (1 << 22, 1, 3, 3), (1 << 22, 2, 3, 3), (1 << 22, 3, 3, 5),
+                                             (1 << 27, 4, 3, 4), (1 << 27, 2, 3, 3)])
+def test_short_loops_of_batches(plans, px, beta, few, one):
+    for k, (*_, lead, launches) in zip(range(1, 12), plans([(64, 64, beta, k, 1, px) for k in range(1, 12)])):
+        assert (len(launches) == k and lead >= k) == (k <= few), (k, launches)
+        assert beta < 3 or k <= few or lead == (1 if k <= one else 0)
