@@ -36,6 +36,7 @@
 #include "phgrms.h"
 #include "phgrms_internal.hpp"
 #include "pass_kernel.hpp"
+#include "arena.hpp"
 
 using namespace phg;
 
@@ -54,44 +55,6 @@ double now_s() {
 
 size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// First-fit allocator over byte offsets of the arena.
-struct FirstFit {
-  std::map<size_t, size_t> free_;   // offset -> size
-  size_t in_use = 0;
-  void init(size_t base, size_t size) {
-    free_.clear();
-    if (size) free_[base] = size;
-  }
-  bool alloc(size_t bytes, size_t* off) {
-    for (auto it = free_.begin(); it != free_.end(); ++it) {
-      if (it->second < bytes) continue;
-      *off = it->first;
-      const size_t rem = it->second - bytes, noff = it->first + bytes;
-      free_.erase(it);
-      if (rem) free_[noff] = rem;
-      in_use += bytes;
-      return true;
-    }
-    return false;
-  }
-  void release(size_t off, size_t bytes) {
-    in_use -= bytes;
-    auto it = free_.emplace(off, bytes).first;
-    auto nx = std::next(it);
-    if (nx != free_.end() && it->first + it->second == nx->first) {
-      it->second += nx->second;
-      free_.erase(nx);
-    }
-    if (it != free_.begin()) {
-      auto pv = std::prev(it);
-      if (pv->first + pv->second == it->first) {
-        pv->second += it->second;
-        free_.erase(it);
-      }
-    }
-  }
-};
-
 enum ReqState { kPending = 0, kActive = 1, kFinishing = 2, kDone = 3, kFailed = 4 };
 
 struct Req {
@@ -107,8 +70,8 @@ struct Req {
   long long tiles = 0;
   size_t off = 0, bytes = 0;
   unsigned long long* counts = nullptr;
-  uint8_t* maps = nullptr;   // deep shapes: change maps, or null (then every launch tests
-                             // every pixel in its first pass)
+  uint8_t* maps = nullptr;   // deep shapes: change maps in a range the arena lends, or null
+                             // (then every launch tests every pixel in its first pass)
   uint8_t* wsimg = nullptr;
   uint8_t* out = nullptr;
   double t_submit = 0, t_done = 0;
@@ -151,7 +114,7 @@ struct phgrms_server {
   uint8_t* hslot[kSlots] = {nullptr, nullptr};
   hipStream_t stream = nullptr;
   hipEvent_t ev[kSlots] = {nullptr, nullptr};
-  FirstFit heap;
+  Arena heap;
   std::mutex mu;
   std::condition_variable cv;
   std::deque<uint64_t> pending;
@@ -186,6 +149,12 @@ void set_shape(Req& r, int shape) {
   r.tiles = tile_geom(r.p, shape).ntiles;
 }
 
+// A request that has no more launches to enqueue needs no maps.
+void give_back_maps(phgrms_server* S, Req& r) {
+  if (r.maps != nullptr) S->heap.give_back(size_t(r.maps - S->arena));
+  r.maps = nullptr;
+}
+
 // Admit the head of the queue if it fits (lock held).
 bool try_admit(phgrms_server* S, Req& r) {
   if ((int)S->active.size() >= S->cfg.max_active) return false;
@@ -195,19 +164,22 @@ bool try_admit(phgrms_server* S, Req& r) {
                                                  : shape_for(r.p.beta, npx, 1));
   }
   if (S->active_tiles + r.tiles > (long long)S->tiles_cap) return false;
-  if (S->heap.in_use + r.bytes > S->cfg.cap_bytes) return false;
   size_t off = 0;
-  // A deep shape's change maps, 5 % more, where half of the cap is free and
-  // the arena has the room: they are never what a request waits for.
-  const size_t maps = is_deep(r.shape) && deep_fits(r.p) && r.L > 1
-                          ? up256(2 * (sizeof(uint32_t) + 1) * deep_map_words(r.p.rows, r.p.cols)) : 0;
-  const bool with_maps = maps > 0 && S->heap.in_use + r.bytes + maps <= S->cfg.cap_bytes / 2 &&
-                         S->heap.alloc(r.bytes + maps, &off);
-  if (!with_maps && !S->heap.alloc(r.bytes, &off)) return false;
+  std::vector<uint64_t> lost;
+  if (!S->heap.alloc(r.bytes, &off, lost)) return false;
+  // (what the steps in flight still do with those maps comes before anything
+  // of this request on the stream)
+  for (uint64_t id : lost) S->reqs[id].maps = nullptr;
   r.off = off;
   uint8_t* base = S->arena + off;
-  r.maps = with_maps ? base + r.bytes : nullptr;
-  if (with_maps) r.bytes += maps;
+  // A deep shape's change maps (10 bytes per row and tile column) are in bytes
+  // that no request holds, while there are any: they are never what a request
+  // waits for.
+  r.maps = nullptr;
+  size_t maps_off = 0;
+  if (is_deep(r.shape) && r.L > 1 &&
+      S->heap.lend(up256(2 * (sizeof(uint32_t) + 1) * deep_map_words(r.p.rows, r.p.cols)), r.id, &maps_off))
+    r.maps = S->arena + maps_off;
   r.counts = reinterpret_cast<unsigned long long*>(base);
   const size_t cbytes = up256(sizeof(uint64_t) * kCountSlots * size_t(std::max(r.p.k, 1)));
   const size_t n = size_t(std::max<int64_t>((int64_t)r.p.rows * r.p.cols, 1));
@@ -299,6 +271,7 @@ int run_step(phgrms_server* S, std::unique_lock<std::mutex>& lk) {
       S->active.erase(std::find(S->active.begin(), S->active.end(), r.id));
       S->active_tiles -= r.tiles;
       S->heap.release(r.off, r.bytes);
+      give_back_maps(S, r);
       S->done_queue.push_back(r.id);
       S->fault_id = 0;
       S->generation++;
@@ -393,6 +366,7 @@ int run_step(phgrms_server* S, std::unique_lock<std::mutex>& lk) {
   for (uint64_t id : finishing) {
     S->active.erase(std::find(S->active.begin(), S->active.end(), id));
     S->active_tiles -= S->reqs[id].tiles;
+    give_back_maps(S, S->reqs[id]);
   }
   // requests in their first step: clear their count slots (and copy a
   // host request's input in) before anything
@@ -575,7 +549,7 @@ int phgrms_server_create(const phgrms_server_cfg* cfg, void* d_arena, size_t are
     const unsigned long long v = std::strtoull(fi, &end, 10);
     if (end != fi && *end == '\0') S->fault_id = v;
   }
-  S->heap.init(reserved, arena_bytes - reserved);
+  S->heap.init(reserved, arena_bytes - reserved, size_t(S->cfg.cap_bytes));
   hipError_t e = hipSetDevice(cfg->device);
   for (int i = 0; i < kSlots && e == hipSuccess; ++i) {
     S->dslot[i] = S->arena + size_t(i) * S->slot_bytes;
@@ -709,7 +683,7 @@ int phgrms_server_get_stats(phgrms_server* S, phgrms_server_stats* st) {
   st->queued = S->pending.size();
   st->active = S->active.size();
   st->steps = S->n_steps;
-  st->bytes_in_use = S->heap.in_use;
+  st->bytes_in_use = S->heap.in_use();
   return S->error;
 }
 

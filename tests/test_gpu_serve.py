@@ -339,3 +339,23 @@ def test_fault_injection_fails_one_request_only(monkeypatch):
     ref, rit, rch = oracle.denoise(reqs[0][0], reqs[0][1], reqs[0][2], reqs[0][3])
     assert np.array_equal(got[0], ref)
     srv.close()
+
+
+def test_cap_filled_by_documented_footprints():
+    """Requests whose footprints (two images and the count slots) fill the cap
+    exactly, held until all are done: those admitted first have change maps,
+    which the last ones take back."""
+    m = phg()
+    rows, cols, k, n = 512, 512, 40, 6
+    foot = 512 * 8 * k + 2 * rows * cols
+    srv = m.Server((64 << 20) + n * foot, device=DEV, max_active=16, passes_per_step=4, cap_bytes=n * foot)
+    imgs = [synth.noisy_image(rows, cols, 0.3, 80 + i) for i in range(n)]
+    want = [oracle.denoise(im, 20, 1 + i % 2, k) for i, im in enumerate(imgs)]
+    for _ in range(3):
+        ids = [srv.submit(torch.from_numpy(im).to(DEV), 20, 1 + i % 2, k) for i, im in enumerate(imgs)]
+        done = wait_all(srv, ids, timeout=20.0)
+        assert srv.stats()["bytes_in_use"] == n * foot
+        for rid, (ref, rit, rch) in zip(ids, want):
+            assert np.array_equal(done[rid][0], ref) and done[rid][1] == rit and done[rid][2] == list(rch)[:rit]
+            srv.release(rid)
+    srv.close()
