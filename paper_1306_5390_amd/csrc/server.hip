@@ -85,17 +85,36 @@ size_t request_bytes(const phgrms_params& p) {
   return up256(sizeof(uint64_t) * kCountSlots * k1) + 2 * up256(n);
 }
 
+// The one-pass shape in place of a deep one for loops of up to `few` passes.
+int unless_short(int shape, const phgrms_params& p, int few) {
+  return is_deep(shape) && p.k <= few ? one_pass_shape(p.beta, (long long)p.rows * p.cols, true) : shape;
+}
+
 // The tuned shape if it runs `passes` passes per launch (or passes <= 0),
 // else the default shape with that many passes: (1, 8, 4) for one pass
 // (measured best for serving mixed sizes), the first such shape otherwise.
-int shape_for(int beta, long long npx, int passes) {
-  int tuned = fused_shape(beta, npx);
-  if (passes == 1 && is_deep(tuned)) tuned = one_pass_shape(beta, npx, true);
+// passes <= 0: short loops are faster by one-pass steps, as for an image alone
+// (deep_few_passes; a burst of 16 requests of 2048^2, beta 4, k 1: 349 us by
+// them, 491 by a deep step; beta 3, k 1: 263 and 366).
+int shape_for(const phgrms_params& p, int passes) {
+  const int tuned = unless_short(fused_shape(p.beta, (long long)p.rows * p.cols), p,
+                                 passes == 1 ? PHGRMS_K_MAX : passes <= 0 ? deep_few_passes(p, true) : 0);
   if (passes <= 0 || kShapes[tuned].T == passes) return tuned;
   if (passes == 1) return kDefaultShape;
   for (int s = 0; s < kNumShapes; ++s)
     if (kShapes[s].T == passes) return s;
   return tuned;
+}
+
+// Adaptive mode's shape while many are active: the batch path's.  (Beside
+// one-pass requests the first pass over a deep tile's halo is dearer: 16
+// requests of 2048^2, k 4: beta 3: 727 us by one-pass steps, 798 with deep
+// ones; beta 4: 963 and 1148; of 512^2, k 16: 481 and 522, 518 and 572; but of
+// 2048^2, k 16: 2395 and 2011, 2483 and 2311.)
+int busy_shape(const phgrms_params& p) {
+  const long long n = (long long)p.rows * p.cols;
+  const int few = p.beta < 3 ? deep_few_passes(p, true) : n < (1 << 20) ? PHGRMS_K_MAX : std::max(deep_few_passes(p, true), 4);
+  return unless_short(batch_shape(p.beta, n), p, few);
 }
 
 }  // namespace
@@ -158,11 +177,8 @@ void give_back_maps(phgrms_server* S, Req& r) {
 // Admit the head of the queue if it fits (lock held).
 bool try_admit(phgrms_server* S, Req& r) {
   if ((int)S->active.size() >= S->cfg.max_active) return false;
-  if (S->cfg.passes_per_step < 0) {
-    const long long npx = (long long)r.p.rows * r.p.cols;
-    set_shape(r, S->active.size() >= kBusyActive ? batch_shape(r.p.beta, npx)
-                                                 : shape_for(r.p.beta, npx, 1));
-  }
+  if (S->cfg.passes_per_step < 0)
+    set_shape(r, S->active.size() >= kBusyActive ? busy_shape(r.p) : shape_for(r.p, 1));
   if (S->active_tiles + r.tiles > (long long)S->tiles_cap) return false;
   size_t off = 0;
   std::vector<uint64_t> lost;
@@ -586,15 +602,14 @@ int submit_request(phgrms_server* S, const uint8_t* d_img, const uint8_t* h_img,
   r.in = d_img;
   r.h_in = h_img;
   r.h_out = h_out;
-  const long long npx = (long long)p.rows * p.cols;
   if (S->cfg.passes_per_step >= 0) {
-    set_shape(r, shape_for(p.beta, npx, S->cfg.passes_per_step));
+    set_shape(r, shape_for(p, S->cfg.passes_per_step));
   } else {
     // adaptive: the shape is chosen at admission; the footprint check takes
     // the larger tile count of the two candidates
-    set_shape(r, batch_shape(p.beta, npx));
+    set_shape(r, busy_shape(p));
     const long long t_batch = r.tiles;
-    set_shape(r, shape_for(p.beta, npx, 1));
+    set_shape(r, shape_for(p, 1));
     r.tiles = std::max(r.tiles, t_batch);
   }
   r.bytes = request_bytes(p);

@@ -359,3 +359,28 @@ def test_cap_filled_by_documented_footprints():
             assert np.array_equal(done[rid][0], ref) and done[rid][1] == rit and done[rid][2] == list(rch)[:rit]
             srv.release(rid)
     srv.close()
+
+
+@pytest.mark.parametrize("passes", [0, -1])
+def test_short_loops(passes):
+    """Loops that run by one-pass steps, one and more passes than those have
+    (the rule's limits at these sizes), at once: a request takes as many steps as its
+    launches, and those that go on run beside the others."""
+    m = phg()
+    srv = m.Server(96 << 20, device=DEV, passes_per_step=passes, max_active=64)
+    specs = [(256, 384, b, k) for b in (1, 2, 3, 4) for k in (1, 2, 3, 5)] + [(256, 8192, 4, k) for k in (5, 6)]
+    imgs = [synth.noisy_image(r, c, 0.3, 7 * i) for i, (r, c, _, _) in enumerate(specs)]
+    ids = [srv.submit(torch.from_numpy(im).to(DEV), 20, b, k) for im, (_, _, b, k) in zip(imgs, specs)]
+    done = wait_all(srv, ids, timeout=60.0)
+    for rid, im, (_, _, b, k) in zip(ids, imgs, specs):
+        ref, rit, rch = oracle.denoise(im, 20, b, k)
+        assert np.array_equal(done[rid][0], ref) and done[rid][1] == rit and done[rid][2] == list(rch)[:rit], (b, k)
+        srv.release(rid)
+    # alone: a step per pass of a short loop, a step for up to four of a longer one
+    for b, k, steps in ((1, 1, 1), (4, 2, 2), (4, 3, 1 if passes == 0 else 3)):
+        before = srv.stats()["steps"]
+        rid = srv.submit(torch.from_numpy(imgs[0]).to(DEV), 20, b, k)
+        wait_all(srv, [rid])
+        srv.release(rid)
+        assert srv.stats()["steps"] - before == steps, (b, k)
+    srv.close()
