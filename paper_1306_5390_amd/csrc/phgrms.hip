@@ -14,6 +14,7 @@
 #include "phgrms_internal.hpp"
 #include "pass_kernel.hpp"
 #include "deep_kernel.hpp"
+#include "host_slots.hpp"
 
 namespace phg {
 
@@ -622,50 +623,27 @@ int enqueue_deep_cycle(const uint8_t* d_in, uint8_t* d_out, const phgrms_params&
 }
 
 // A synchronous call's results in page-locked host memory that the GPU writes
-// directly: one block of kHostSlots slots for the process, made at the first
-// use (129 KiB, kept until the process ends), each held by one call at a
-// time, from any thread.
-constexpr int kHostSlots = 16;
+// directly (129 KiB for the process).
 constexpr int kHostSlotWords = 1 + PHGRMS_K_MAX;   // iteration count, totals
+void* page_locked(size_t bytes) {
+  void* p = nullptr;
+  if (hipHostMalloc(&p, bytes, hipHostMallocPortable) == hipSuccess) return p;
+  (void)hipGetLastError();
+  return nullptr;
+}
+HostSlots g_host_slots(kHostSlotWords, page_locked);
 struct HostSlot {
-  int64_t* words = nullptr;   // null: none free
-  HostSlot() {
-    std::lock_guard<std::mutex> lk(mu());
-    static int64_t* block = [] {
-      void* p = nullptr;
-      if (hipHostMalloc(&p, sizeof(int64_t) * kHostSlots * kHostSlotWords, hipHostMallocPortable) != hipSuccess) {
-        (void)hipGetLastError();
-        p = nullptr;
-      }
-      return static_cast<int64_t*>(p);
-    }();
-    if (block == nullptr) return;
-    for (int i = 0; i < kHostSlots && words == nullptr; ++i)
-      if (!used()[i]) {
-        used()[i] = true;
-        index = i;
-        words = block + size_t(i) * kHostSlotWords;
-      }
-  }
+  int64_t* words = g_host_slots.take();   // null: none free
+  HostSlot() = default;
   ~HostSlot() {
-    if (words == nullptr || index < 0) return;
-    std::lock_guard<std::mutex> lk(mu());
-    used()[index] = false;
+    if (words != nullptr && !abandoned) g_host_slots.give_back(words);
   }
-  void abandon() { index = -1; }   // never handed out again
+  void abandon() { abandoned = true; }    // never handed out again
   HostSlot(const HostSlot&) = delete;
   HostSlot& operator=(const HostSlot&) = delete;
 
  private:
-  int index = -1;
-  static std::mutex& mu() {
-    static std::mutex m;
-    return m;
-  }
-  static bool* used() {
-    static bool u[kHostSlots] = {};
-    return u;
-  }
+  bool abandoned = false;
 };
 
 int set_fused_shape(int beta, int cls, int shape) {

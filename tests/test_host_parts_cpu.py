@@ -23,3 +23,7 @@ def _run(tmp_path, name):
 
 def test_server_arena(tmp_path):
     _run(tmp_path, "arena_driver")
+
+
+def test_result_slots(tmp_path):
+    _run(tmp_path, "slots_driver")
