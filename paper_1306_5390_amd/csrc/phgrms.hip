@@ -359,6 +359,7 @@ WsLayout ws_layout(const phgrms_params& p) {
   l.counts_off = 256;
   l.diff_off = l.counts_off + sizeof(uint64_t) * size_t(kCountSlots) * size_t(std::max(p.k, 1));
   l.changed_off = l.diff_off + sizeof(uint64_t) * size_t(kCountSlots) * size_t(std::max(p.k, 1));
+  l.sync_off = l.changed_off - sizeof(uint64_t);
   l.img_off = l.changed_off + up(sizeof(uint64_t) * size_t(std::max(p.k, 1)));
   l.map_off = l.img_off + up(size_t(std::max<int64_t>((int64_t)p.rows * p.cols, 1)));
   l.map_bytes = change_map_bytes(p.rows, p.cols);
@@ -743,18 +744,16 @@ int phgrms_denoise(const uint8_t* d_in, uint8_t* d_out, phgrms_params p, void* d
   const WsLayout l = ws_layout(p);
   uint8_t* ws = static_cast<uint8_t*>(d_ws);
   auto* counts = reinterpret_cast<unsigned long long*>(ws + l.counts_off);
-  auto* changed = reinterpret_cast<unsigned long long*>(ws + l.changed_off);
   hipStream_t s = static_cast<hipStream_t>(stream);
   // The finish kernel writes the iteration count and the totals into page-
-  // locked memory; where no slot is free, next to each other in the workspace
-  // (the last of the period-2 stop's slots, which this call does not use, is
-  // right before the totals), from where one copy reads both back.  (128^2,
-  // k 5: 44 us a call with a slot, 53 with one copy, 64 with two.)
+  // locked memory; where no slot is free, next to each other in the workspace,
+  // from where one copy reads both back.  (128^2, k 5: 44 us a call with a
+  // slot, 53 with one copy, 64 with two.)
   HostSlot slot;
   int64_t copy[kHostSlotWords];
   int64_t* res = slot.words != nullptr ? slot.words : copy;
-  unsigned long long* d_res = reinterpret_cast<unsigned long long*>(slot.words != nullptr ? slot.words
-                                                                   : reinterpret_cast<int64_t*>(changed - 1));
+  auto* d_res = reinterpret_cast<unsigned long long*>(slot.words != nullptr ? static_cast<void*>(slot.words)
+                                                                            : ws + l.sync_off);
   rc = enqueue_denoise(d_in, d_out, p, fused_shape(p.beta, (long long)p.rows * p.cols), ws + l.img_off, counts,
                        d_res + 1, reinterpret_cast<int*>(d_res), ws + l.map_off, s);
   if (rc != PHGRMS_OK) {

@@ -46,6 +46,9 @@ struct WsLayout {
   size_t state_off;    // int32 iteration count
   size_t counts_off;   // uint64 count slots, kCountSlots per pass
   size_t diff_off;     // uint64 slots of the period-2 stop, right after the counts
+  size_t sync_off;     // a synchronous call's iteration count, right before the totals, so that
+                       // one copy reads both: the last of the slots before them, of which such
+                       // a call uses none
   size_t changed_off;  // uint64 changed[max(k,1)] totals
   size_t img_off;      // rows*cols bytes, the second ping-pong image
   size_t map_off;      // two change maps of map_bytes / 2 each
