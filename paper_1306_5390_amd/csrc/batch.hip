@@ -540,6 +540,10 @@ int phgrms_batch_plan(const phgrms_item* items, int32_t n, const char* tune_cach
     }
   }
   for (auto& g : pl->groups) {
+    if (g.deep() && std::max(g.plan.first, g.plan.rest) > deep_max_passes(g.beta)) {
+      delete pl;   // (they would give wrong pixels)
+      return fail(PHGRMS_EINVAL, "batch launches of more passes than a tile's halo holds");
+    }
     for (const TileTable& tt : g.tables)
       if (tt.tiles.size() > size_t(1) << 30) {
         const size_t ntiles = tt.tiles.size();

@@ -41,8 +41,9 @@ int hip_fail(hipError_t e, const char* what) {
 const KernelShape kShapes[] = {
     {1, 8, 1, 0},  {1, 16, 1, 0}, {1, 8, 2, 0}, {1, 8, 4, 0}, {1, 16, 4, 0},
     {2, 16, 4, 0}, {4, 16, 4, 0}, {1, 8, 4, 1}, {1, 8, 2, 1}, {1, 4, 8, 0},
-    {1, 4, 4, 0},  {1, 8, 4, 2}, {1, 8, 2, 2}, {4, 8, 8, 3},
+    {1, 4, 4, 0},  {1, 8, 4, 2}, {1, 8, 2, 2}, {kDeepShapePasses, 8, 8, 3},
 };
+static_assert(kDeepShapePasses <= deep_max_passes(PHGRMS_BETA_MAX), "the halo of a deep tile holds its passes");
 static_assert(sizeof(kShapes) / sizeof(kShapes[0]) <= 16, "per-shape tables hold 16 entries");
 const int kNumShapes = int(sizeof(kShapes) / sizeof(kShapes[0]));
 
@@ -183,6 +184,8 @@ hipError_t launch_deep(int beta, int shape, DeepArgs a, hipStream_t s, bool cycl
   int grid = pass_grid(beta, shape, a.ntiles);
   const int full = pass_grid(beta, shape, 0, true) / kListedOversubscription * kDeepOversubscription;
   if (k == nullptr || grid <= 0 || full <= 0) return hipErrorInvalidValue;
+  // (more passes than the halo holds would give wrong pixels, not an error)
+  if (a.t.depth > deep_max_passes(beta) || a.t.npasses > a.t.depth) return hipErrorInvalidValue;
   a.check = a.t.map_in != nullptr && grid > full ? 1 : 0;
   if (a.check) grid = full;
   void* args[] = {&a};

@@ -87,6 +87,7 @@ const void* multi_kernel_ptr(int beta, int shape, bool maps = false);
 // Deep shapes (deep_kernel.hpp, deep.hip): kernels of one image and of many.
 inline bool is_deep(int shape) { return kShapes[shape].track == 3; }
 constexpr int kDeepShape = 13;
+constexpr int kDeepShapePasses = 4;   // of a launch, where the caller chooses them (server, phgrms_run_passes)
 constexpr int kDeepWaves = 8;      // waves of a workgroup
 constexpr int kDeepWideWaves = 16; // the same where no CU has more than one (beta 1 .. 3)
 const void* deep_kernel_ptr(int beta, bool wide);
