@@ -155,7 +155,10 @@ struct TileTable {
   size_t off = 0;                   // in the workspace
 };
 
-// Workgroups that the device runs with a CU each.
+// Workgroups that the device runs with a CU each.  Not asked of the device: a
+// plan is made without any HIP call (before a fork, or on a machine without a
+// GPU), and whichever device is current runs it.  On a partition of fewer CUs
+// the tiles of a small batch are lower than they need be: slower, not wrong.
 constexpr int kBatchCus = 256;
 
 // Owned rows of the deep tiles of a small batch: the fewest (but 4) with
