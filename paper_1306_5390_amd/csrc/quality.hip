@@ -92,10 +92,15 @@ __device__ __forceinline__ uint32_t sq_diff4(uint32_t a, uint32_t b) {
 // thread takes 16-byte vectors, kSumUnroll of each image in flight, and a
 // word's four squares take three dot products; otherwise bytes.  Two reads
 // of memory bound it (4096^2: 33.6 MB in 8.5 us, 3.9 TB/s; by bytes with a
-// 64-bit multiply each and 8192 atomics it took 101).
+// 64-bit multiply each and 8192 atomics it took 101).  By bytes the loads in
+// flight bound it, so that large images need every wave the device holds
+// (a byte apart, with 256 and with 512 workgroups: 2^28 pixels 471 and 270 us,
+// 287 with the 8192 small ones; 2^24: 22 and 18, 104; 2^22: 8 and 11, 102).
 constexpr int kSumUnroll = 4;
 constexpr int kSumThreads = 1024;
 constexpr int kSumGroups = 256;    // one atomic each, 20 ns apart on the one address
+constexpr int kSumByteGroups = 512;
+constexpr long long kSumManyBytes = 1ll << 24;
 __global__ __launch_bounds__(kSumThreads) void sq_diff_kernel(const uint8_t* a, const uint8_t* b,
                                                       long long n, unsigned long long* sum) {
   unsigned long long s = 0;
@@ -185,7 +190,9 @@ int phgrms_sq_diff_sum(const uint8_t* d_a, const uint8_t* d_b, int64_t n, int64_
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "zero launch");
   if (n > 0) {
-    hipLaunchKernelGGL(sq_diff_kernel, dim3(std::min(grid_for(n), kSumGroups)), dim3(kSumThreads), 0, s, d_a, d_b,
+    const bool bytes = ((reinterpret_cast<uintptr_t>(d_a) ^ reinterpret_cast<uintptr_t>(d_b)) & 15u) != 0;
+    const int groups = bytes && n >= kSumManyBytes ? kSumByteGroups : kSumGroups;
+    hipLaunchKernelGGL(sq_diff_kernel, dim3(std::min(grid_for(n), groups)), dim3(kSumThreads), 0, s, d_a, d_b,
                        (long long)n, sum);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "sum launch");
   }

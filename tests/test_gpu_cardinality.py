@@ -62,3 +62,16 @@ def test_noise_at_every_alignment(n, oi, oo):
     got = dst.cpu().numpy()
     assert np.array_equal(got[oo:oo + n], np.asarray(want).reshape(-1))
     assert (got[:oo] == 6).all() and (got[oo + n:] == 6).all()
+
+
+# From 2^24 pixels on images that start at different places have more workgroups.
+@pytest.mark.parametrize("n", [(1 << 24) - 1, 1 << 24, (1 << 24) + 4097])
+def test_squared_differences_of_many_bytes(n):
+    import torch
+    import paper_1306_5390_amd as m
+    gen = torch.Generator(device="cuda:0").manual_seed(n)
+    a, b = (torch.randint(0, 256, (n + 16,), dtype=torch.uint8, device="cuda:0", generator=gen) for _ in range(2))
+    a[:n // 2], b[:n // 2] = 0, 255
+    for oa, ob in [(0, 0), (0, 1), (7, 2)]:
+        want = int((a[oa:oa + n].long() - b[ob:ob + n].long()).square().sum())
+        assert int(m.sq_diff_sum(a[oa:oa + n].view(1, n), b[ob:ob + n].view(1, n)).item()) == want
