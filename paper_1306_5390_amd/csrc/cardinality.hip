@@ -122,8 +122,17 @@ __global__ __launch_bounds__(kCardWaves * 64) void card_kernel(const uint8_t* im
 
 // One thread per pixel, bytes read from memory: for images narrower than
 // kCardNarrow columns, where most lanes of a wave above would have no pixel,
-// and for sides near 2^31, which its column arithmetic does not hold.
+// for sides near 2^31, which its column arithmetic does not hold, and for small
+// images, which have too few waves above to hide the chain of 8 rows that each
+// of them goes through (us, a thread per pixel and a wave per strip: 128^2:
+// beta 1: 3.7 and 3.9, 2: 4.2 and 5.5, 3: 6.4 and 7.5, 4: 9.2 and 9.5; 321 x
+// 481: 3.6 and 5.3, 5.0 and 7.0, 7.5 and 9.0, 10.6 and 11.3; 512^2: 3.6 and
+// 4.0, 5.4 and 5.6, 8.2 and 7.6, 11.6 and 9.6; 2048 x 200: 3.9 and 4.2, 6.1 and
+// 5.7, 9.0 and 7.7, 12.8 and 9.8).
 constexpr int kCardNarrow = 64;
+constexpr long long card_small(int beta) {         // pixels
+  return beta == 1 ? 6 << 16 : beta == 2 ? 5 << 16 : beta == 3 ? 4 << 16 : 1 << 16;
+}
 template <class Out>
 __global__ void card_pixel_kernel(const uint8_t* __restrict__ img, int rows, int cols, int alpha, int beta,
                                   Out* __restrict__ card) {
@@ -168,7 +177,7 @@ int cardinality(const uint8_t* d_img, int32_t rows, int32_t cols, int32_t alpha,
   if (n == 0) return PHGRMS_OK;
   if (d_img == nullptr || d_card == nullptr) return fail(PHGRMS_EINVAL, "null pointer");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (cols < kCardNarrow || cols >= (1 << 30)) {
+  if (cols < kCardNarrow || cols >= (1 << 30) || n < card_small(beta)) {
     const int blocks = int(std::min<long long>((n + 255) / 256, 65536));
     hipLaunchKernelGGL(card_pixel_kernel<Out>, dim3(blocks), dim3(256), 0, s, d_img, rows, cols, alpha, beta, d_card);
   } else {

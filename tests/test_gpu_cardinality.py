@@ -75,3 +75,38 @@ def test_squared_differences_of_many_bytes(n):
     for oa, ob in [(0, 0), (0, 1), (7, 2)]:
         want = int((a[oa:oa + n].long() - b[ob:ob + n].long()).square().sum())
         assert int(m.sq_diff_sum(a[oa:oa + n].view(1, n), b[ob:ob + n].view(1, n)).item()) == want
+
+
+def _check_cardinality(beta, rows, cols, alpha, offset):
+    import torch
+    import paper_1306_5390_amd as m
+    lib = m.load_library()
+    img = synth.noisy_image(rows, cols, 0.3, beta + offset)
+    want = oracle.cardinality(img, alpha, beta)
+    buf = torch.zeros(rows * cols + 4, dtype=torch.uint8, device="cuda:0")
+    t = buf[offset:offset + rows * cols].view(rows, cols)
+    t.copy_(torch.from_numpy(img))
+    assert np.array_equal(m.cardinality(t, alpha, beta).cpu().numpy(), want)
+    card = torch.full((rows * cols + 8,), -1, dtype=torch.int16, device="cuda:0")
+    m.check(lib.phgrms_cardinality(t.data_ptr(), rows, cols, alpha, beta, card.data_ptr() + 2,
+                                   ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)))
+    got = card.cpu().numpy()
+    assert np.array_equal(got[1:1 + rows * cols].reshape(rows, cols), want)
+    assert got[0] == -1 and (got[1 + rows * cols:] == -1).all()
+
+
+# The most pixels of a thread per pixel, and some more: a wave per strip.
+@pytest.mark.parametrize("beta,rows,cols", [(1, 384, 1023), (1, 384, 1024), (2, 320, 1023), (2, 320, 1024), (3, 511, 512),
+                                            (3, 512, 513), (4, 255, 257), (4, 257, 256)])
+def test_cardinality_of_small_images(beta, rows, cols):
+    _check_cardinality(beta, rows, cols, 20, 0)
+
+
+# A wave per strip at the edges of its strips: rows about 8, columns about 256, every
+# byte offset, the extremes of the band.
+@pytest.mark.parametrize("beta", [1, 2, 3, 4])
+@pytest.mark.parametrize("rows,cols", [(1, 400001), (7, 60001), (8, 50180), (9, 50175), (6145, 64), (6151, 65), (1601, 255),
+                                       (1600, 256), (1537, 259), (1543, 516)])
+def test_cardinality_by_strips(beta, rows, cols):
+    for offset, alpha in enumerate((0, 1, 20, 255)):
+        _check_cardinality(beta, rows, cols, alpha, offset)
