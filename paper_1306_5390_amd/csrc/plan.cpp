@@ -143,13 +143,17 @@ CyclePlan cycle_plan(const phgrms_params& p) {
 // 4, k 6: 122 and 148, k 10: 199 and 183; 8192^2, beta 1, k 10: 667 and 691,
 // k 12: 786 and 739).  At beta 4 large images are faster by the one or by the
 // other, as their noise is (4096^2, k 32: 905 and 674, four tenths noise 193
-// and 296), and stay with the one-pass launches.
+// and 296), and stay with the one-pass launches; so do small ones of a few
+// passes, where much noise is gone after two of them and the launches after
+// those end at once (k 5, a tenth noise and two fifths: 720 x 1280: 72 and 67,
+// 21 and 29; 1448^2: 100 and 103, 37 and 38; 321 x 481, k 2: 45 and 35, 21 and 23).
 bool cycle_plan_pays(const phgrms_params& p) {
   const int64_t n = (int64_t)p.rows * p.cols;
   if (p.k <= 1 || n <= 0 || !deep_fits(p)) return false;
+  if (std::min(p.rows, p.cols) <= 2 * p.beta) return false;   // (no pass changes anything)
   const bool huge = n >= (1 << 25);
-  if ((p.cols & 3) != 0) return p.beta < 4 || !huge;
-  if (n < (1 << 21)) return p.k > 2 || n < (1 << 18);
+  if ((p.cols & 3) != 0) return p.beta < 4 || (!huge && p.k > 2);
+  if (n < (1 << 21)) return p.beta == 4 ? p.k > 6 : p.k > 2 || n < (1 << 18);
   switch (p.beta) {
     case 1: return p.k > (huge ? 10 : 4);
     case 2: return p.k > 3;

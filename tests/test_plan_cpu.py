@@ -75,8 +75,8 @@ def test_short_loops_run_by_one_pass_launches(plans, rows, cols, beta, few):
 
 
 def test_images_without_interior_pixels(plans):
-    for (_, lead, *_) in plans([(9, 8, 4, 32, 1), (8, 900, 4, 32, 1), (2, 70000, 1, 32, 1)]):
-        assert lead == 32
+    for (_, lead, _, _, pays, *_) in plans([(9, 8, 4, 32, 1), (8, 900, 4, 32, 1), (2, 70000, 1, 32, 1)]):
+        assert lead == 32 and not pays
 
 
 # (pixels of the batch, beta): the longest loop without a deep launch, and the longest with
@@ -88,3 +88,10 @@ def test_short_loops_of_batches(plans, px, beta, few, one):
     for k, (*_, lead, launches) in zip(range(1, 12), plans([(64, 64, beta, k, 1, px) for k in range(1, 12)])):
         assert (len(launches) == k and lead >= k) == (k <= few), (k, launches)
         assert beta < 3 or k <= few or lead == (1 if k <= one else 0)
+
+
+@pytest.mark.parametrize("rows,cols,beta,few", [(128, 128, 1, 1), (1024, 1024, 2, 2), (128, 128, 4, 6), (1448, 1448, 4, 6),
+                                                (321, 481, 4, 2), (997, 1031, 4, 2), (321, 481, 3, 1), (2048, 2048, 4, 8)])
+def test_short_loops_with_the_period2_stop(plans, rows, cols, beta, few):
+    got = plans([(rows, cols, beta, k, 1) for k in range(1, 12)])
+    assert [pays for *_, pays, _, _ in got] == [k > few for k in range(1, 12)]
