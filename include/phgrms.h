@@ -98,7 +98,7 @@ size_t phgrms_workspace_bytes(phgrms_params p);
  *   h_iterations host int (may be NULL): passes executed;
  *   stream       hipStream_t.
  * Depending on the tuned kernel shape, several passes run per kernel launch
- * (temporal blocking) or, with a change-tracking shape, rows whose
+ * (temporal blocking; a short loop may run one pass per launch all the same) or, with a change-tracking shape, rows whose
  * neighbourhood did not change in the previous pass are copied through
  * untested (see phgrms_run_passes); convergence is detected on the device.
  * Returns after synchronising `stream`. */
@@ -269,7 +269,8 @@ int phgrms_cardinality_scatter(const uint8_t* d_img, int32_t rows, int32_t cols,
 /* ---- many images ---------------------------------------------------------
  * A batch denoises many images of different sizes, each with its own alpha,
  * beta and k, with one multi-image pass launch per (stream, launch index,
- * beta, kernel shape) instead of one launch sequence per image: the images
+ * beta, kernel shape, launch plan) instead of one launch sequence per image
+ * (a launch plan is how a loop is cut into launches): the images
  * are spread over three streams by work, forked from the caller's stream
  * and joined back before the final kernel.  Images live in caller-owned
  * device arenas at byte offsets.  The plan is immutable after creation; the
@@ -345,7 +346,9 @@ typedef struct {
                                 0: the tuned kernel shape's passes per launch;
                                 -1: adaptive (one pass per step while fewer than
                                 8 requests are active, else the batch path's
-                                shape for requests admitted then) */
+                                shape for requests admitted then); with 0 and
+                                -1 short loops run one pass per step where that
+                                is faster */
   int32_t max_queue;         /* pending requests before submit returns EBUSY */
   uint64_t cap_bytes;        /* admission cap on device bytes (<= arena) */
 } phgrms_server_cfg;
