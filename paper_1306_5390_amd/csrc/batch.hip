@@ -3,9 +3,9 @@
 // Each image of a batch runs the pass loop of Section 2 with its own size,
 // alpha, beta and k.  Instead of one launch sequence per image, the images
 // are spread over three streams (balanced by work; see share_launches) and,
-// per stream, launch j of every image with the same beta and kernel shape goes
-// into one multi_deep_kernel (or multi_pass_kernel) launch over a static table
-// of all their tiles.  The plan precomputes, per group, the tile tables and the
+// per stream, launch j of every image with the same beta, kernel shape and
+// launch plan goes into one multi_deep_kernel (or multi_pass_kernel) launch over
+// a static table of all their tiles.  The plan precomputes, per group, the tile tables and the
 // image descriptors of every launch index; a run uploads them once per set of pointers and replays the
 // whole sequence (forked to the streams and joined) as a HIP graph.
 #include <hip/hip_runtime.h>

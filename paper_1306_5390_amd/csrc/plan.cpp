@@ -82,16 +82,14 @@ LaunchPlan deep_plan(const phgrms_params& p, bool maps) {
   return pl;
 }
 
-// In a large batch two
-// dense one-pass launches come first, since its images fill the device and
-// the halo of a deep tile is all cost while every pixel is tested, and at
-// beta 1 the later launches take 16 passes (150 images of 192 Mpixel, k 32:
-// 2.39 ms; without the dense launches 2.99, with 8 passes 2.48).  A small
-// batch is latency-bound, and takes fewer launches of smaller halo (12 images
-// of 1.5 Mpixel, k 16: 176 us against 204; 48 images of 20 Mpixel: 413
-// against 379).
-// Images of up to three passes have dense launches only, from 2^22 pixels on
-// (us per run, a tenth noise, with deep launches, with dense ones, and before
+// In a large batch two dense one-pass launches come first, since its images
+// fill the device and the halo of a deep tile is all cost while every pixel is
+// tested, and at beta 1 the later launches take 16 passes (150 images of 192
+// Mpixel, k 32: 2.39 ms; without the dense launches 2.99, with 8 passes 2.48).
+// A small batch is latency-bound, and takes fewer launches of smaller halo (12
+// images of 1.5 Mpixel, k 16: 176 us against 204; 48 images of 20 Mpixel: 413
+// against 379).  Images of up to three passes have dense launches only, from
+// 2^22 pixels on (us per run, a tenth noise, with deep launches, with dense ones, and before
 // there were deep ones: 8 images of 8 Mpixel, beta 3, k 2: 86, 68, 72; 12 of 50
 // Mpixel, beta 4, k 3: 746, 549, 557; 4 of 17 Mpixel, beta 2, k 3: 130, 102,
 // 115); at beta 4 the shortest already from 2^21 (12 of 3 Mpixel, k 2: 71, 60,
@@ -134,9 +132,9 @@ CyclePlan cycle_plan(const phgrms_params& p) {
 }
 
 // One-pass launches are as fast, with their smaller halo and a finish of one
-// launch, for the first few passes of a large
-// image whose rows start on dword boundaries, and more so at the larger betas
-// (us per call, one-pass and deep, a tenth of the pixels noise or, at beta 1,
+// launch, for the first few passes of a large image whose rows start on dword
+// boundaries, and more so at the larger betas (us per call, one-pass and deep,
+// a tenth of the pixels noise or, at beta 1,
 // four tenths; 512^2, beta 1, k 2: 21 and 23; 4096^2: beta 1, k 4: 103 and
 // 120, k 6: 145 and 147, a tenth noise 118 and 81; beta 2, k 3: 106 and 110,
 // k 4: 144 and 120; beta 3, k 6: 239 and 278, k 10: 392 and 349; 2048^2, beta

@@ -113,7 +113,8 @@ int shape_for(const phgrms_params& p, int passes) {
 // 2048^2, k 16: 2395 and 2011, 2483 and 2311.)
 int busy_shape(const phgrms_params& p) {
   const long long n = (long long)p.rows * p.cols;
-  const int few = p.beta < 3 ? deep_few_passes(p, true) : n < (1 << 20) ? PHGRMS_K_MAX : std::max(deep_few_passes(p, true), 4);
+  int few = deep_few_passes(p, true);
+  if (p.beta >= 3) few = n < (1 << 20) ? PHGRMS_K_MAX : std::max(few, 4);
   return unless_short(batch_shape(p.beta, n), p, few);
 }
 
